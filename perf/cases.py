@@ -162,8 +162,7 @@ def system(case, q, m, seed):
                     precision=R.RBSOG_MIXED if case.get("mixed") else R.RBSOG_FP64)
 
 
-def dt_of(case):
-    return 0.01 * min(1.0, math.sqrt(case["gamma"]))
+DT = 0.01
 
 
 def bath_of(case):
@@ -265,7 +264,7 @@ def run_traj(case, s):
     s["f"].copy_(s["f0"])
     if bath_of(case) != "none":   # selecting a bath starts its state afresh
         R.rbsog_set_bath(h, BATHS[bath_of(case)], 1.0, 1.0 / case["gamma"])
-    R.rbsog_step(h, s["x"], s["v"], s["f"], 0, case["nsteps"], dt_of(case), s.get("eh"))
+    R.rbsog_step(h, s["x"], s["v"], s["f"], 0, case["nsteps"], DT, s.get("eh"))
     out = dict(x=s["x"], v=s["v"], f=s["f"])
     if case["energies"]:
         out["energy"] = s["eh"]
@@ -375,7 +374,7 @@ def exact(case, seed):
     if kind == "forces":
         f, fn, e = E.force(x, 0)
         return dict(f=f, f_near=fn, energy=torch.tensor(e, dtype=torch.float64, device=DEV))
-    dt, kT, bath = dt_of(case), 1.0 / case["gamma"], bath_of(case)
+    dt, kT, bath = DT, 1.0 / case["gamma"], bath_of(case)
     Lt = torch.tensor(L, dtype=torch.float64, device=DEV)[:, None]
     f = E.force(x, 0)[0]
     xi, eta, gkT, rows = 0.0, 0.0, 3.0 * case["N"] * kT, []
