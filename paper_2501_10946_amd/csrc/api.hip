@@ -494,12 +494,12 @@ int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bo
         na.red = ra;
         na.nrho = (int)((rho_blocks(ra.nchunk, ra.P) + 7) / 8 * 8);
         // Spread through a launch of several rounds of workgroups, the partial
-        // sums fill the issue slots the near field's gathers leave (near launches
-        // of the plasmas: N = 2e5, 4 178 workgroups, 115 -> 108 us; N = 6e5,
-        // 536 -> 450 us; N = 1e6, 19 350 workgroups, 0.91 -> 0.74 ms).  A launch
-        // the chip holds at once gains nothing from that and runs best with the
-        // longer partial-sum workgroups dispatched first (N = 1e5: 1 789
-        // workgroups, 49.5 us first, 53.6 us spread).
+        // sums fill the issue slots the near field's gathers leave (N = 3e5,
+        // 7 032 workgroups: 600 -> 598 us an evaluation; the evaluation with three
+        // lanes per particle gained far more: N = 1e6, 0.91 -> 0.74 ms).  A launch
+        // the chip holds at once runs best with the longer partial-sum
+        // workgroups dispatched first (N = 1e5, 2 176 workgroups: a step 83 us
+        // first, 88 us spread).
         na.interleave = (int64_t)na.nrho + near_blocks((int)h->p.N) >= kInterleaveBlocks;
         if (const char *e = std::getenv("RBSOG_NEAR_INTERLEAVE"))   // 0 / 1: a tuning knob
             na.interleave = std::atoi(e) != 0;
@@ -772,7 +772,16 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
         h->sd.c[j] = s->c[j];
         h->sd.s_log2e[j] = s->s[j] * log2e;
         h->sd.cs2[j] = 2.0 * s->c[j] * s->s[j];
+        h->sd.f.c[j] = (float)h->sd.c[j];
+        h->sd.f.s_log2e[j] = (float)h->sd.s_log2e[j];
+        h->sd.f.cs2[j] = (float)h->sd.cs2[j];
     }
+    h->sd.f.inv_lambda = (float)h->sd.inv_lambda;
+    h->sd.f.inv_lambda_log2e = (float)h->sd.inv_lambda_log2e;
+    h->sd.f.ya1 = (float)h->sd.ya1;
+    h->sd.f.ya2 = (float)h->sd.ya2;
+    h->sd.f.inv_lambda2 = (float)h->sd.inv_lambda2;
+    h->sd.f.inv_lambda2_log2e = (float)h->sd.inv_lambda2_log2e;
     static_assert(kNearPolyDeg + 1 == sizeof(h->sd.hpoly) / sizeof(double), "near polynomial size");
     // the polynomial pair function serves the FP64 kernels only (mixed precision
     // evaluates the exponentials in FP32), so a mixed system skips the fit

@@ -92,7 +92,9 @@ constexpr SinCosPoly make_sincos_poly()
 }
 
 // 2^y for finite y <= 0 (FP64): 2^y = 2^n 2^f with n = rint(y), f = y - n exact.
-__device__ inline double exp2_nonpos(double y, const Exp2Poly &P)
+// Poly: Exp2Poly, in any address space.
+template <class Poly>
+__device__ inline double exp2_nonpos(double y, const Poly &P)
 {
     double n = rint(y);
     double f = y - n;

@@ -7,35 +7,38 @@
 // The cell grid is the fine one, cells of width w = L / floor(2L / (r_c + skin))
 // >= (r_c + skin) / 2, so the neighbour stencil is 5 x 5 x 5 cells; cell order
 // makes each x-row of 5 cells one contiguous index range (two where it wraps
-// around the box).  Work is split into (particle, plane) lanes, plane dz =
-// -2..2 of the stencil; rows and x-cells whose distance from the particle
-// already exceeds the list radius are skipped per particle.
+// around the box).
 //
 //   k_nlist  a wave lists the particles of two x-adjacent cells: lanes take
 //            the candidates of the pair's 5 x 5 x 6-cell window 64 at a time
 //            (loads coalesced along the rows) and test each against every
 //            home particle in turn; the accepted ones are appended in lane
-//            order straight into the particles' lists (tile-major: 64
-//            particles side by side per row, a tile's rows contiguous), in
-//            window order, with a count per particle;
-//   k_near   a workgroup owns 256 consecutive particles and one of the
-//            kNearLanes lanes per particle (4 waves); lane s evaluates entries
-//            s, s + kNearLanes, ... of the particle's list, so the lanes get
-//            equal shares (a split by plane would not: the outer planes hold 0
-//            to ~17 entries depending on where the particle sits in its cell).
-//            Each lane runs down its entries with the next index and the next
-//            neighbour position already in flight, and stores its partial
-//            force; the far-field kernel adds the partials in lane order.  In FP64
-//            the pair function is, when its fit is accurate, one polynomial
+//            order straight into the particles' lists, in window order, with
+//            a count per particle;
+//   k_near   a wave evaluates the lists of 16 consecutive particles, four
+//            lanes each: lane s takes entries s, s + 4, ... two at a time, with
+//            the rows of the next two and the indices of the two after in
+//            flight, and the four add their sums before three of them store the
+//            force.  In FP64 the pair function is, when its fit is accurate, one polynomial
 //            in r (r^3 times the force factor, 24 to 28 FMAs, no exponential),
 //            otherwise the number of Gaussians is a template parameter for
 //            the common counts; coefficients stay in scalar registers.  When a
 //            particle's list overflowed at the build, its lanes walk the
 //            candidates of the current positions, plane by plane.  A
 //            single system's launch also computes the structure-factor
-//            partial sums in its first workgroups: the gathers above leave
-//            the arithmetic units idle much of the time, the partial sums
+//            partial sums in some of its workgroups: the gathers above leave
+//            the arithmetic units idle part of the time, the partial sums
 //            keep them busy (the reduction follows as a launch of its own).
+//
+// Why four lanes side by side: a gather instruction looks its rows up one cache
+// line after the other, so what it costs is the number of lines its 64 lanes
+// touch (random rows of 32 bytes: 111 cycles of a compute unit for 64 rows,
+// runs of four consecutive rows: 60).  Consecutive entries of one list are
+// often consecutive rows; the earlier split (three lanes per particle in three
+// different waves) had none of that, wrote and read three partial forces per
+// particle, and a wave waited for the longest of 64 lists where it now waits
+// for the longest of 16.  Of 4, 8 and 16 lanes, 4 is the fastest (N = 1e5: 82
+// us a step, 8: 87, 16: 98; the earlier split: 87).
 //
 // Lists hold every j within r_c + skin at the build.  The step path rebuilds
 // them (and the cell order) only when some particle has moved more than
@@ -52,9 +55,24 @@ namespace rbsog {
 
 constexpr int kNearPlanes = 5;                 // stencil planes dz = -2..2
 constexpr int kListThreads = 64 * kListWaves;  // list build: one cell pair per wave
-constexpr int kEvalThreads = 256;              // evaluation: 256 particles x 1 plane
 constexpr int kShiftBits = 5;                  // image-shift code 0..26 in the top bits of a range start
 constexpr uint32_t kIndexMask = (1u << (32 - kShiftBits)) - 1u;
+
+// The argument block where it lies in memory (the kernel's argument segment, or
+// the ensemble's table): its fields are scalar loads.  near_args_again makes
+// the compiler load them anew from there on, instead of keeping every field of
+// the block in scalar registers from the kernel's start: the pair polynomials
+// need those, and what does not fit is kept in lanes of vector registers and
+// read back with an instruction each.
+typedef const __attribute__((address_space(4))) NearArgs NearMem;
+typedef const double __attribute__((address_space(4))) *ScalarMem;
+
+__device__ inline NearMem &near_args_again(NearMem &a)
+{
+    NearMem *p = &a;
+    __asm__ volatile("" : "+s"(p));
+    return *p;
+}
 
 __device__ inline double shift_of(int code, double L) { return (double)(code - 1) * L; }
 
@@ -80,7 +98,7 @@ struct Lane {
     double gz;              // z-gap from the particle to the plane
 };
 
-__device__ inline Lane make_lane(const NearArgs &a, int p, int plane)
+__device__ inline Lane make_lane(NearMem &a, int p, int plane)
 {
     Lane l;
     l.p = p;
@@ -105,7 +123,7 @@ __device__ inline Lane make_lane(const NearArgs &a, int p, int plane)
 // The candidate ranges of row `row` (dy = row - 2) for a lane within radius
 // sqrt(R2) (R2 <= the list radius squared, which the fine grid is built for):
 // 0, 1 or 2 ranges.
-__device__ inline int row_ranges(const NearArgs &a, const Lane &l, int row, double R2, Range out[2])
+__device__ inline int row_ranges(NearMem &a, const Lane &l, int row, double R2, Range out[2])
 {
     const int nf = a.g.nc[0], nfy = a.g.nc[1];
     const double m = a.margin;
@@ -149,15 +167,15 @@ __device__ inline int row_ranges(const NearArgs &a, const Lane &l, int row, doub
     return n;
 }
 
-// FP64 1/sqrt(x) for x > 0: hardware estimate refined by two Newton steps.
+// FP64 1/sqrt(x) for x > 0: the hardware estimate (measured within 2^-24.2 of
+// it over [1, 4)) and one third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 -
+// x y^2, whose remainder 5 e^3/16 is below 2^-70: five instructions where two
+// second-order steps take seven.
 __device__ inline double rsqrt_f64(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    double hx = 0.5 * x;
-    double e = fma(-hx * y, y, 0.5);
-    y = fma(y, e, y);
-    e = fma(-hx * y, y, 0.5);
-    return fma(y, e, y);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Gaussians of the pair function: NG > 0 is a compile-time count, 0 the
@@ -168,11 +186,11 @@ __device__ inline double rsqrt_f64(double x)
 // unchanged, so the result is the same bit for bit).
 constexpr int kPolyNG = -28;
 template <int NG>
-__device__ inline int gauss_count(const NearArgs &a) { return NG > 0 ? NG : a.sog.n; }
+__device__ inline int gauss_count(NearMem &a) { return NG > 0 ? NG : a.sog.n; }
 
 // Horner in y of the degree-D polynomial c (ascending powers).
 template <int D>
-__device__ inline double near_poly_eval(const double *c, double y)
+__device__ inline double near_poly_eval(ScalarMem c, double y)
 {
     static_assert(D >= 1 && D <= 28, "the argument block holds 29 powers");
     double p = c[D];
@@ -181,15 +199,48 @@ __device__ inline double near_poly_eval(const double *c, double y)
     return p;
 }
 
+// A launch with energies needs two polynomials' coefficients, more than the
+// scalar registers hold: the force polynomial stays in them, the energy
+// polynomial's come from the scalar cache at each pass over two pairs.
+// p0, p1 = the degree-D polynomial c at y0, y1.
+template <int D>
+__device__ inline void near_poly_pair(ScalarMem c, double y0, double y1, double &p0, double &p1)
+{
+    __asm__ volatile("" : "+s"(c));   // loaded here, not kept from an earlier pass
+    p0 = c[D];
+    p1 = c[D];
+#pragma unroll
+    for (int k = D - 1; k >= 0; --k) {
+        const double ck = c[k];
+        p0 = fma(p0, y0, ck);
+        p1 = fma(p1, y1, ck);
+    }
+}
+
+// The sums of a lane over its pairs: force, energy and virial per unit charge of
+// the particle itself, whose own charge multiplies them once at the end.
+struct NearSums {
+    double fx, fy, fz, en, vir;
+};
+
+// A pair's displacement, squared distance, force factor and energy per unit
+// charge of the particle, from the raw difference of the positions and the
+// neighbour's charge.  Evaluated whatever r2 is (a pair beyond r_c or a
+// stand-in entry gives values nobody adds), so that the terms of several pairs
+// interleave; near_add adds those of a pair that counts.
+struct PairTerms {
+    double dx, dy, dz, r2, fac, u;
+    double y, qir;   // the energy polynomial's argument and factor (near_energy)
+};
+
 // IMG: the axes (bit d for axis d) on which the minimum-image step is taken;
 // the callers leave an axis out only where the step provably changes nothing
 // (near_image_axes).
-template <bool MIXED, bool ENERGY, int NG, int IMG = 7>
-__device__ inline void pair_force(const NearArgs &a, const double4 &pi, const double4 &pj, double &fx, double &fy,
-                                  double &fz, double &en, double &vir)
+template <bool MIXED, bool ENERGY, int NG, int IMG>
+__device__ inline PairTerms pair_terms(NearMem &a, double dx, double dy, double dz, double qj)
 {
+    PairTerms t;
     // d by the minimum image (|d| < r_c <= L_d/3)
-    double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
     if (IMG & 1) dx = fma(-a.g.L[0], rint(dx * a.inv_L[0]), dx);
     if (IMG & 2) dy = fma(-a.g.L[1], rint(dy * a.inv_L[1]), dy);
     if (IMG & 4) dz = fma(-a.g.L[2], rint(dz * a.inv_L[2]), dz);
@@ -197,47 +248,41 @@ __device__ inline void pair_force(const NearArgs &a, const double4 &pi, const do
     // may pick another product to fuse depending on how d was formed, and the
     // IMG variants must give the same bits
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    if (!(r2 < a.rc2)) return;   // listed within r_c + skin, beyond r_c now
-    double qq = pi.w * pj.w;
+    t.dx = dx;
+    t.dy = dy;
+    t.dz = dz;
+    t.r2 = r2;
+    t.u = 0.0;
     if (MIXED) {
         float r2f = (float)r2;
         float irf = __builtin_amdgcn_rsqf(r2f);
         float rf = r2f * irf;
-        float ey = __builtin_amdgcn_exp2f(-rf * (float)a.sog.inv_lambda_log2e);
-        float f1 = ey * (1.0f + rf * (float)a.sog.inv_lambda);
+        float ey = __builtin_amdgcn_exp2f(-rf * a.sog.f.inv_lambda_log2e);
+        float f1 = ey * (1.0f + rf * a.sog.f.inv_lambda);
         if (a.sog.two) {   // the second Yukawa term of a two-term kernel
-            const float ez = __builtin_amdgcn_exp2f(-rf * (float)a.sog.inv_lambda2_log2e);
-            f1 = fmaf((float)a.sog.ya2, ez * (1.0f + rf * (float)a.sog.inv_lambda2), (float)a.sog.ya1 * f1);
-            ey = fmaf((float)a.sog.ya2, ez, (float)a.sog.ya1 * ey);
+            const float ez = __builtin_amdgcn_exp2f(-rf * a.sog.f.inv_lambda2_log2e);
+            f1 = fmaf(a.sog.f.ya2, ez * (1.0f + rf * a.sog.f.inv_lambda2), a.sog.f.ya1 * f1);
+            ey = fmaf(a.sog.f.ya2, ez, a.sog.f.ya1 * ey);
         }
         f1 = f1 * (irf * irf * irf);
         float gs = 0.0f, fs = 0.0f;
 #pragma unroll
         for (int g = 0; g < (NG < 0 ? 0 : gauss_count<NG>(a)); ++g) {
-            float eg = __builtin_amdgcn_exp2f(-(float)a.sog.s_log2e[g] * r2f);
-            gs = fmaf((float)a.sog.cs2[g], eg, gs);
-            if (ENERGY) fs = fmaf((float)a.sog.c[g], eg, fs);
+            float eg = __builtin_amdgcn_exp2f(-a.sog.f.s_log2e[g] * r2f);
+            gs = fmaf(a.sog.f.cs2[g], eg, gs);
+            if (ENERGY) fs = fmaf(a.sog.f.c[g], eg, fs);
         }
-        double fac = qq * (double)(f1 - gs);
-        fx = fma(fac, dx, fx);
-        fy = fma(fac, dy, fy);
-        fz = fma(fac, dz, fz);
-        if (ENERGY) {
-            en = fma(qq, (double)(ey * irf - fs), en);
-            vir = fma(fac, r2, vir);   // d . F of the pair
-        }
+        t.fac = qj * (double)(f1 - gs);
+        if (ENERGY) t.u = qj * (double)(ey * irf - fs);
     } else if constexpr (NG < 0) {
         // H(r) / r^3 and K(r) / r with H, K the polynomials in y = 2 r / r_c - 1
         double ir = rsqrt_f64(r2);
         double r = r2 * ir;
         const double y = fma(r, a.sog.y_scale, -1.0);
-        double fac = qq * (near_poly_eval<-NG>(a.sog.hpoly, y) * (ir * ir * ir));
-        fx = fma(fac, dx, fx);
-        fy = fma(fac, dy, fy);
-        fz = fma(fac, dz, fz);
+        t.fac = qj * (near_poly_eval<-NG>(a.sog.hpoly, y) * (ir * ir * ir));
         if (ENERGY) {
-            en = fma(qq, near_poly_eval<-NG>(a.sog.kpoly, y) * ir, en);
-            vir = fma(fac, r2, vir);   // d . F of the pair
+            t.y = y;
+            t.qir = qj * ir;
         }
     } else {
         double ir = rsqrt_f64(r2);
@@ -259,14 +304,34 @@ __device__ inline void pair_force(const NearArgs &a, const double4 &pi, const do
                 if (ENERGY) fs = fma(a.sog.c[g], eg, fs);
             }
         }
-        double fac = qq * (f1 - gs);
-        fx = fma(fac, dx, fx);
-        fy = fma(fac, dy, fy);
-        fz = fma(fac, dz, fz);
-        if (ENERGY) {
-            en = fma(qq, ey * ir - fs, en);
-            vir = fma(fac, r2, vir);   // d . F of the pair
-        }
+        t.fac = qj * (f1 - gs);
+        if (ENERGY) t.u = qj * (ey * ir - fs);
+    }
+    return t;
+}
+
+// The energies of two pairs whose pair function is a polynomial.
+template <int NG>
+__device__ inline void near_energy(ScalarMem kpoly, PairTerms &t0, PairTerms &t1)
+{
+    if constexpr (NG < 0) {
+        double k0, k1;
+        near_poly_pair<-NG>(kpoly, t0.y, t1.y, k0, k1);
+        t0.u = t0.qir * k0;
+        t1.u = t1.qir * k1;
+    }
+}
+
+template <bool ENERGY>
+__device__ inline void near_add(NearSums &s, const PairTerms &t)
+{
+    __asm__ volatile("");   // kept a branch: as selects the sums cost three times the instructions
+    s.fx = fma(t.fac, t.dx, s.fx);
+    s.fy = fma(t.fac, t.dy, s.fy);
+    s.fz = fma(t.fac, t.dz, s.fz);
+    if (ENERGY) {
+        s.en += t.u;
+        s.vir = fma(t.fac, t.r2, s.vir);   // d . F of the pair
     }
 }
 
@@ -499,7 +564,10 @@ __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
 #pragma unroll
         for (int hh = 0; hh < kListHomes; ++hh)
             if (lane == hh) mine = (int)(slot[hh] - (uint32_t)(hh * rows));
-        if (lane < nh) a.nbr_cnt[hb + lane] = mine > rows ? rows + 1 : mine;
+        if (lane < nh) {
+            a.nbr_cnt[hb + lane] = mine > rows ? rows + 1 : mine;
+            if (mine == 0) pass_row[(size_t)lane * rows] = hb + lane;   // entry 0 is always a valid index
+        }
         // the positions of the next pass overwrite these
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -528,7 +596,7 @@ __device__ inline void nlist_body(const NearArgs &a, int lb)
 // at least as large as its true one and stays beyond r_c either way.  Lanes
 // past N count as interior.  1 for the x axis alone (a wave of cell-ordered
 // particles crosses the box along x), 7 whenever y or z is needed.
-__device__ inline int near_image_axes(const NearArgs &a, const double4 &pi, int p)
+__device__ inline int near_image_axes(NearMem &a, const double4 &pi, int p)
 {
     const double m = sqrt(a.rc2) * (1.0 + 1e-6);
     const bool live = p < a.N;
@@ -541,93 +609,122 @@ __device__ inline int near_image_axes(const NearArgs &a, const double4 &pi, int 
 // Row j of the cell-ordered positions by a 32-bit byte offset from the
 // wave-uniform base (j < 2^27: the offset fits), one address operation
 // fewer per neighbour than a 64-bit index.
-__device__ inline double4 xs_row(const NearArgs &a, int j)
+__device__ inline double4 xs_row(NearMem &a, int j)
 {
     return *(const double4 *)((const char *)a.xs + ((uint32_t)j << 5));
 }
 
-// A lane's share of particle p's list (total <= rows entries): lane s takes
-// blocks s, s + kNearLanes, ... (kListBlock consecutive entries each).  A
-// block's indices arrive as two 16-byte loads while the block before is
-// evaluated, and within a block the positions of two entries are loading
-// while the two before are evaluated.  Entries past the count are not used:
-// the particle itself (or the last one, for lanes past N) stands in for them
-// and is never evaluated.
+// A lane's share of particle p's list: lane `sub` of its kNearShare lanes takes
+// entries sub, sub + kNearShare, ...; `steps` (uniform over the wave, at least
+// 1) covers the longest list of the wave's particles.  Past the end of its
+// particle's list a lane repeats the last entry (entry 0 is valid in an empty
+// list too), which is not added.  Two entries per pass; the rows of the next
+// two start loading into the same registers once the differences are formed,
+// and the indices of the two after them follow.  row0 is the wave's first
+// list, `at` this lane's first entry and `last` its particle's last, in bytes
+// from there.
 template <bool MIXED, bool ENERGY, int NG, int IMG>
-__device__ inline void near_list(const NearArgs &a, const double4 &pi, int p, int s, int total, int rows, double &fx,
-                                 double &fy, double &fz, double &en, double &vir)
+__device__ inline void near_list(NearMem &args, const double4 &pi, const char *row0, uint32_t at, uint32_t last,
+                                 int steps, NearSums &s)
 {
-    const int nblk = (total + kListBlock - 1) / kListBlock;
-    const int self = p < a.N ? p : a.N - 1;
-    const int32_t *blk = a.nbr + list_at(p, 0, rows);   // block b at blk + b * bstride
-    const size_t bstride = (size_t)kListBlock;
-    int4 n0 = make_int4(self, self, self, self), n1 = n0;
-    if (s < nblk) {
-        n0 = *(const int4 *)(blk + (size_t)s * bstride);
-        n1 = *(const int4 *)(blk + (size_t)s * bstride + 4);
-    }
-    for (int b = s; b < nblk; b += kNearLanes) {
-        const int ne = min(kListBlock, total - b * kListBlock);
-        int jj[kListBlock] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
-        const int bn = b + kNearLanes;
-        if (bn < nblk) {
-            n0 = *(const int4 *)(blk + (size_t)bn * bstride);
-            n1 = *(const int4 *)(blk + (size_t)bn * bstride + 4);
+    NearMem &a = near_args_again(args);
+    constexpr uint32_t kStep = kNearShare * sizeof(int32_t);
+    auto entry = [&](uint32_t b) { return *(const int32_t *)(row0 + min(b, last)); };
+    double4 q0 = xs_row(a, entry(at)), q1 = xs_row(a, entry(at + kStep));
+    int j0 = entry(at + 2 * kStep), j1 = entry(at + 3 * kStep);
+    for (int k = 0; k < steps; k += 2) {   // uniform
+        double dx0 = pi.x - q0.x, dy0 = pi.y - q0.y, dz0 = pi.z - q0.z, w0 = q0.w;
+        double dx1 = pi.x - q1.x, dy1 = pi.y - q1.y, dz1 = pi.z - q1.z, w1 = q1.w;
+        // the differences before the loads below: no copies of the rows
+        __asm__ volatile("" : "+v"(dx0), "+v"(dy0), "+v"(dz0), "+v"(w0), "+v"(dx1), "+v"(dy1), "+v"(dz1), "+v"(w1)
+                         :: "memory");
+        q0 = xs_row(a, j0);
+        q1 = xs_row(a, j1);
+        j0 = entry(at + 4 * kStep);
+        j1 = entry(at + 5 * kStep);
+        PairTerms t0 = pair_terms<MIXED, ENERGY, NG, IMG>(a, dx0, dy0, dz0, w0);
+        PairTerms t1 = pair_terms<MIXED, ENERGY, NG, IMG>(a, dx1, dy1, dz1, w1);
+        // both evaluated before either is added under its mask: the two chains
+        // interleave and share their scalar coefficients
+        __asm__ volatile("" : "+v"(t0.fac), "+v"(t1.fac));
+        if (ENERGY) {
+            if (!MIXED) near_energy<NG>(a.sog.kpoly, t0, t1);
+            __asm__ volatile("" : "+v"(t0.u), "+v"(t1.u));
         }
-#pragma unroll
-        for (int e = 0; e < kListBlock; ++e)
-            if (e >= ne) jj[e] = self;
-        double4 qa = xs_row(a, jj[0]), qb = xs_row(a, jj[1]);
-#pragma unroll
-        for (int e = 0; e < kListBlock; e += 2) {
-            const double4 ca = qa, cb = qb;
-            if (e + 2 < kListBlock) {
-                qa = xs_row(a, jj[e + 2]);
-                qb = xs_row(a, jj[e + 3]);
-            }
-            if (e < ne) pair_force<MIXED, ENERGY, NG, IMG>(a, pi, ca, fx, fy, fz, en, vir);
-            if (e + 1 < ne) pair_force<MIXED, ENERGY, NG, IMG>(a, pi, cb, fx, fy, fz, en, vir);
-        }
+        if (at <= last && t0.r2 < a.rc2) near_add<ENERGY>(s, t0);
+        if (at + kStep <= last && t1.r2 < a.rc2) near_add<ENERGY>(s, t1);
+        at += 2 * kStep;
     }
 }
 
-// lb: the logical workgroup (256 particles, one of kNearLanes lanes each).
+// Sum over a particle's kNearShare lanes, in every one of them.
+template <int CTRL>
+__device__ inline double dpp_add(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, true);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ inline double share_sum(double v)
+{
+    v = dpp_add<0xB1>(v);                          // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);                          // quad_perm [2,3,0,1]
+    if (kNearShare >= 8) v = dpp_add<0x141>(v);    // row_half_mirror: the other quad of 8
+    if (kNearShare >= 16) v = dpp_add<0x140>(v);   // row_mirror: the other half of 16
+    return v;
+}
+
+// lb: the logical workgroup, kNearHomes consecutive particles of kNearShare lanes
+// each.
 // SPLIT: choose the minimum-image axes per wave (near_image_axes); the served
 // ensemble's small replicas have nearly every wave at a face, so their batch
 // launch takes every axis and saves the code.
 template <bool MIXED, bool ENERGY, int NG, bool SPLIT = true>
-__device__ inline void near_body(const NearArgs &a, int lb)
+__device__ inline void near_body(NearMem &a0, int lb)
 {
-    __shared__ double2 red[kEvalThreads];
-    const int t = threadIdx.x;
-    const int grp = lb / kNearLanes;
-    const int s = lb - grp * kNearLanes;   // this lane of the particle
-    const int p = grp * kEvalThreads + t;
+    NearMem &a = near_args_again(a0);
+    static_assert(kNearShare == 4 || kNearShare == 8 || kNearShare == 16, "share_sum adds 4, 8 or 16 lanes");
+    const int t = threadIdx.x, sub = t & (kNearShare - 1);
+    const int rows = list_rows(a.kp);
+    const int p = lb * kNearHomes + t / kNearShare;
     double4 pi = make_double4(0.0, 0.0, 0.0, 0.0);
     int total = 0;
     if (p < a.N) {
         pi = a.xs[p];
         total = a.nbr_cnt[p];
     }
-    double fx = 0.0, fy = 0.0, fz = 0.0, en = 0.0, vir = 0.0;
-    const int rows = list_rows(a.kp);
-    if (total <= rows) {
-        // the minimum-image axes: uniform over the lanes that take this branch
+    const bool walk = total > rows;   // the list overflowed at the build
+    if (walk) total = 0;
+    int longest = 0;   // of the wave's particles
+#pragma unroll
+    for (int k = 0; k < 64; k += kNearShare) longest = max(longest, __builtin_amdgcn_readlane(total, k));
+    const int steps = (longest + kNearShare - 1) / kNearShare;
+    NearSums s{};
+    if (steps > 0) {   // uniform
+        const int pw = min(__builtin_amdgcn_readfirstlane(p), a.N - 1);   // the wave's first particle
+        const char *row0 = (const char *)(a.nbr + list_at(pw, 0, rows));
+        const uint32_t mine = (uint32_t)((min(p, a.N - 1) - pw) * rows);   // entry 0 of this particle, from there
+        // a particle without entries has none to add: its lanes start past entry 0
+        const uint32_t at = 4u * (mine + (uint32_t)sub + (total ? 0u : 1u));
+        const uint32_t last = 4u * (mine + (uint32_t)max(total - 1, 0));
         const int img = SPLIT ? near_image_axes(a, pi, p) : 7;
-        if (img == 0) near_list<MIXED, ENERGY, NG, 0>(a, pi, p, s, total, rows, fx, fy, fz, en, vir);
-        else if (img == 1) near_list<MIXED, ENERGY, NG, 1>(a, pi, p, s, total, rows, fx, fy, fz, en, vir);
-        else near_list<MIXED, ENERGY, NG, 7>(a, pi, p, s, total, rows, fx, fy, fz, en, vir);
-    } else {
-        // the particle's list overflowed at the build: its lanes walk the
-        // cells of the stencil planes dz = plane - 2 (lane s the planes s,
-        // s + kNearLanes, ...) around the current position.  Particles may
-        // have moved up to skin/2 out of the cells they were sorted into (and
-        // wrapped around the box), so the cells are culled with the list
-        // radius and the pair function itself (minimum image, r < r_c)
-        // decides.
-        for (int plane = s; plane < kNearPlanes; plane += kNearLanes) {
+        if (img == 0) near_list<MIXED, ENERGY, NG, 0>(a, pi, row0, at, last, steps, s);
+        else if (img == 1) near_list<MIXED, ENERGY, NG, 1>(a, pi, row0, at, last, steps, s);
+        else near_list<MIXED, ENERGY, NG, 7>(a, pi, row0, at, last, steps, s);
+    }
+    if (walk) {
+        // the particle's lanes walk the cells of the stencil around the
+        // current position.  Particles may have moved up to skin/2 out of
+        // the cells they were sorted into (and wrapped around the box), so
+        // the cells are culled with the list radius and the pair function
+        // itself (minimum image, r < r_c) decides.
+#pragma unroll 1
+        for (int plane = 0; plane < kNearPlanes; ++plane) {
             const Lane l = make_lane(a, p, plane);
             if (l.gz * l.gz < a.rl2) {
+#pragma unroll 1
                 for (int row = 0; row < 5; ++row) {
                     Range g[2];
                     const int n = row_ranges(a, l, row, a.rl2, g);
@@ -635,29 +732,43 @@ __device__ inline void near_body(const NearArgs &a, int lb)
                     for (int k = 0; k < 2; ++k) {   // fixed indices: g stays in registers
                         if (k >= n) break;
                         const int j0 = g[k].start_code & (int32_t)kIndexMask;
-                        for (int j = j0; j < g[k].end; ++j)
-                            if (j != p) pair_force<MIXED, ENERGY, NG>(a, pi, a.xs[j], fx, fy, fz, en, vir);
+                        for (int j = j0 + sub; j < g[k].end; j += kNearShare) {
+                            if (j == p) continue;
+                            const double4 q = a.xs[j];
+                            PairTerms u =
+                                pair_terms<MIXED, ENERGY, NG, 7>(a, pi.x - q.x, pi.y - q.y, pi.z - q.z, q.w);
+                            if (ENERGY && !MIXED) near_energy<NG>(a.sog.kpoly, u, u);
+                            if (u.r2 < a.rc2) near_add<ENERGY>(s, u);
+                        }
                     }
                 }
             }
         }
     }
-    if (p < a.N) {
-        double *o = a.fnear + (size_t)s * 3 * a.N + p;
-        o[0] = fx;
-        o[a.N] = fy;
-        o[2 * (size_t)a.N] = fz;
-    }
-    if (ENERGY) {   // each pair is seen from both ends: half of its energy and virial from each
-        red[t] = make_double2(0.5 * en, 0.5 * vir);
-        __syncthreads();
-        for (int off = kEvalThreads / 2; off > 0; off >>= 1) {
-            if (t < off) red[t] = make_double2(red[t].x + red[t + off].x, red[t].y + red[t + off].y);
-            __syncthreads();
+    // the particle's lanes added in a fixed order; three of them store
+    NearMem &o = near_args_again(a);
+    const double fx = pi.w * share_sum(s.fx), fy = pi.w * share_sum(s.fy), fz = pi.w * share_sum(s.fz);
+    if (p < o.N && sub < 3) o.fnear[(size_t)sub * o.N + p] = sub == 0 ? fx : sub == 1 ? fy : fz;
+    if (ENERGY) {
+        __shared__ double2 red[kNearThreads / 64];
+        // each pair is seen from both ends: half of its energy and virial from each
+        double e = share_sum(0.5 * pi.w * s.en), w = share_sum(0.5 * pi.w * s.vir);
+#pragma unroll
+        for (int off = kNearShare; off < 64; off <<= 1) {
+            e += __shfl_xor(e, off);
+            w += __shfl_xor(w, off);
         }
+        if ((t & 63) == 0) red[t >> 6] = make_double2(e, w);
+        __syncthreads();
         if (t == 0) {
-            a.epart[lb] = red[0].x;
-            a.epart[near_blocks(a.N) + lb] = red[0].y;
+            double es = 0.0, ws = 0.0;
+#pragma unroll
+            for (int k = 0; k < kNearThreads / 64; ++k) {
+                es += red[k].x;
+                ws += red[k].y;
+            }
+            o.epart[lb] = es;
+            o.epart[near_blocks(o.N) + lb] = ws;
         }
     }
 }
@@ -668,37 +779,38 @@ __global__ __launch_bounds__(kListThreads) void k_nlist(NearArgs a)
     nlist_body(a, xcd_block((int)blockIdx.x, (int)gridDim.x));
 }
 
-// Mixed precision without energies: held to the registers of 5 waves per SIMD
-// (it needs a few more than 96 otherwise, and its gathers want the waves).
+// Without energies: held to the registers of 5 waves per SIMD (the cell walk of
+// an overflowed list alone would take more; the gathers want the waves).
 template <bool MIXED, bool ENERGY, int NG>
-__global__ __launch_bounds__(kEvalThreads) __attribute__((amdgpu_waves_per_eu(MIXED && !ENERGY ? 5 : 1))) void k_near(
+__global__ __launch_bounds__(kNearThreads) __attribute__((amdgpu_waves_per_eu(!ENERGY ? 5 : 1))) void k_near(
     NearArgs a)
 {
-    static_assert(kEvalThreads == kBlock, "the structure-factor workgroups have kBlock threads");
+    static_assert(kNearThreads == kBlock, "the structure-factor workgroups have kBlock threads");
     const int b = (int)blockIdx.x;
+    int rb = -1, nb = 0;   // a structure-factor workgroup, or a near one
     if (a.nrho == 0 || !a.interleave) {
-        if (b < a.nrho) {   // uniform per workgroup
-            if (b < rho_blocks(a.red.nchunk, a.red.P)) rho_partial_body<true, MIXED, true>(a.red, b);
-            return;
-        }
-        near_body<MIXED, ENERGY, NG>(a, xcd_block(b - a.nrho, (int)gridDim.x - a.nrho));
-        return;
+        if (b < a.nrho) rb = b;
+        else nb = b - a.nrho;
+    } else {
+        // The structure-factor workgroups are spread evenly through the launch in
+        // whole groups of 8 (one per XCD), so that every compute unit holds
+        // arithmetic-bound partial sums beside the near field's gather-bound
+        // waves; the near groups keep their dispatch order, and with it the XCD
+        // mapping, and the partial last group is a near group.
+        const int64_t gr = a.nrho / 8, gn = (gridDim.x - a.nrho + 7) / 8, G = gr + gn;
+        const int64_t g = b / 8;
+        const int64_t before = (g * gr + G - 1) / G;          // structure-factor groups before group g
+        const int64_t upto = ((g + 1) * gr + G - 1) / G;
+        if (upto > before) rb = (int)(before * 8 + (b & 7));
+        else nb = (int)((g - before) * 8 + (b & 7));
     }
-    // The structure-factor workgroups are spread evenly through the launch in
-    // whole groups of 8 (one per XCD), so that every compute unit holds
-    // arithmetic-bound partial sums beside the near field's gather-bound
-    // waves; the near groups keep their dispatch order, and with it the XCD
-    // mapping, and the partial last group is a near group.
-    const int64_t gr = a.nrho / 8, gn = (gridDim.x - a.nrho + 7) / 8, G = gr + gn;
-    const int64_t g = b / 8;
-    const int64_t before = (g * gr + G - 1) / G;          // structure-factor groups before group g
-    const int64_t upto = ((g + 1) * gr + G - 1) / G;
-    if (upto > before) {   // uniform per workgroup
-        const int rb = (int)(before * 8 + (b & 7));
+    if (rb >= 0) {   // uniform per workgroup
         if (rb < rho_blocks(a.red.nchunk, a.red.P)) rho_partial_body<true, MIXED, true>(a.red, rb);
         return;
     }
-    near_body<MIXED, ENERGY, NG>(a, xcd_block((int)((g - before) * 8 + (b & 7)), (int)gridDim.x - a.nrho));
+    // the argument block is the kernel's only argument
+    near_body<MIXED, ENERGY, NG>(*(NearMem *)__builtin_amdgcn_kernarg_segment_ptr(),
+                                 xcd_block(nb, (int)gridDim.x - a.nrho));
 }
 
 __global__ __launch_bounds__(kListThreads) void k_nlist_batch(const NearArgs *__restrict__ tab,
@@ -709,17 +821,11 @@ __global__ __launch_bounds__(kListThreads) void k_nlist_batch(const NearArgs *__
 }
 
 template <bool MIXED, bool ENERGY, int NG>
-__global__ __launch_bounds__(kEvalThreads) void k_near_batch(const NearArgs *__restrict__ tab,
+__global__ __launch_bounds__(kNearThreads) void k_near_batch(const NearArgs *__restrict__ tab,
                                                              const EnsItem *__restrict__ items)
 {
     const EnsItem e = items[blockIdx.x];
-    if constexpr (NG == 0) {
-        near_body<MIXED, ENERGY, NG, false>(tab[e.r], e.b);
-    } else {
-        // read before any store, the copy's fields become scalar loads
-        const NearArgs a = tab[e.r];
-        near_body<MIXED, ENERGY, NG, false>(a, e.b);
-    }
+    near_body<MIXED, ENERGY, NG, false>(*(NearMem *)(uintptr_t)(tab + e.r), e.b);
 }
 
 // A launch with a missing buffer is refused on the host.
@@ -742,7 +848,7 @@ hipError_t launch_nlist(const NearArgs &a, hipStream_t st)
 template <bool MIXED, bool ENERGY>
 static void launch_near_ng(const NearArgs &a, dim3 grid, hipStream_t st)
 {
-    dim3 block(kEvalThreads);
+    dim3 block(kNearThreads);
     const size_t lds = a.nrho > 0 ? rho_lds_bytes(a.red.P, a.red.chunk, MIXED, true) : 0;
     if (!MIXED && a.sog.poly) {   // the polynomials' degree: 24, 26 or 28
         if (a.sog.poly <= 24) hipLaunchKernelGGL((k_near<false, ENERGY, -24>), grid, block, lds, st, a);
@@ -778,13 +884,13 @@ hipError_t launch_near_batch(const NearArgs *tab, const EnsItem *items, int n, i
 {
     if (!tab || !items || n < 1 || ng < 0 || ng > 9 || (ng == 9 && mixed)) return hipErrorInvalidValue;
     if (ng == 9) {   // FP64 replicas whose Gaussian sums are polynomials
-        if (energy) hipLaunchKernelGGL((k_near_batch<false, true, kPolyNG>), dim3(n), dim3(kEvalThreads), 0, st, tab,
+        if (energy) hipLaunchKernelGGL((k_near_batch<false, true, kPolyNG>), dim3(n), dim3(kNearThreads), 0, st, tab,
                                        items);
-        else hipLaunchKernelGGL((k_near_batch<false, false, kPolyNG>), dim3(n), dim3(kEvalThreads), 0, st, tab,
+        else hipLaunchKernelGGL((k_near_batch<false, false, kPolyNG>), dim3(n), dim3(kNearThreads), 0, st, tab,
                                 items);
         return hipGetLastError();
     }
-    dim3 grid(n), block(kEvalThreads);
+    dim3 grid(n), block(kNearThreads);
 #define RBSOG_NEAR_B(M, E, G) \
     if (mixed == M && energy == E && ng == G) { \
         hipLaunchKernelGGL((k_near_batch<M, E, G>), grid, block, 0, st, tab, items); \

@@ -49,6 +49,12 @@ struct SogDev {
     double c[kMaxGauss];        // F(r) = sum c exp(-s r^2)
     double s_log2e[kMaxGauss];  // s log2(e): exp(-s r^2) = 2^(-s log2(e) r^2)
     double cs2[kMaxGauss];      // 2 c s (force factor of the Gaussians)
+    // the same rounded to FP32 for the mixed kernels: scalar registers on the
+    // device, where a conversion of a scalar would take vector registers
+    struct {
+        float inv_lambda, inv_lambda_log2e, ya1, ya2, inv_lambda2, inv_lambda2_log2e;
+        float c[kMaxGauss], s_log2e[kMaxGauss], cs2[kMaxGauss];
+    } f;
     // the pair function as polynomials of y = r y_scale - 1 of degree poly
     // (0: none; the powers above it are zero)
     int poly;
@@ -232,7 +238,7 @@ struct NearArgs {
     SogDev sog;
     const double4 *xs;         // cell order
     const int32_t *cell_start;
-    double *fnear;             // [kNearLanes][3][N] partial forces of the lanes of each particle, cell order
+    double *fnear;             // [3][N] near forces, cell order
     double *epart;             // [2][near_blocks(N)] energy, then virial partials (when energy)
     int mixed;
     int energy;
@@ -260,7 +266,7 @@ struct NearArgs {
 constexpr int64_t kInterleaveBlocks = 3072;
 hipError_t launch_nlist(const NearArgs &a, hipStream_t st);
 // workgroups per system: list build (cell pairs of the fine grid of nf cells per axis), evaluation
-// (256 particles x one of 5 lanes), far field (64 particles)
+// (kNearHomes particles), far field (64 particles)
 // list build: one pair of x-adjacent cells per wave, kListWaves waves per workgroup
 constexpr int kListWaves = 4;
 __host__ __device__ inline int nlist_blocks(const int nf[3])
@@ -271,21 +277,24 @@ __host__ __device__ inline int nlist_blocks(const int nf[3])
 // contiguous at list_at(p, 0, rows) (rows a multiple of kListBlock,
 // list_rows), so a list build's append of a run of accepted candidates of one
 // particle fills consecutive words and the lines of a list are written by the
-// one wave that builds it; the evaluation reads a particle's entries in blocks
-// of kListBlock (32 bytes, two 16-byte loads).  Measured at the N = 1e6 plasma
-// against a layout with the 64 particles of a tile side by side per entry (or
-// per block): the build's scattered one-word stores into 64-particle rows cost
-// more than the evaluation gains from reading rows of 64 lanes.  Arrays hold
-// list_padded(N) particles.
+// one wave that builds it, and the lanes of a particle in the evaluation read
+// neighbouring words.  Measured at the N = 1e6 plasma against a layout with the
+// 64 particles of a tile side by side per entry (or per block): the build's
+// scattered one-word stores into 64-particle rows cost more than an evaluation
+// by 64 particles' lanes gains.  Arrays hold list_padded(N) particles.
 constexpr int kListBlock = 8;
 __host__ __device__ inline int list_rows(int kp) { return (5 * kp + kListBlock - 1) / kListBlock * kListBlock; }
 __host__ __device__ inline size_t list_at(int p, int k, int rows) { return (size_t)p * (size_t)rows + (size_t)k; }
 __host__ __device__ inline int64_t list_padded(int64_t N) { return (N + 63) / 64 * 64; }
-// evaluation: a particle's list is dealt round-robin to kNearLanes lanes (3
-// measured fastest of 1..5 on the N = 1e5 plasma: longer runs per lane than 5,
-// enough waves to hide the gathers unlike 1 or 2)
-constexpr int kNearLanes = 3;
-__host__ __device__ inline int near_blocks(int N) { return kNearLanes * ((N + 255) / 256); }
+// evaluation: a particle's list is dealt round-robin to kNearShare lanes of one
+// wave, which add their sums before the wave stores the particle's force
+// (kNearLanes = 1 partial force per particle).  A workgroup holds kNearHomes
+// particles.
+constexpr int kNearThreads = 256;
+constexpr int kNearShare = 4;
+constexpr int kNearHomes = kNearThreads / kNearShare;
+constexpr int kNearLanes = 1;
+__host__ __device__ inline int near_blocks(int N) { return (N + kNearHomes - 1) / kNearHomes; }
 __host__ __device__ inline int far_blocks(int N) { return (N + 63) / 64; }
 // ensemble: list builds (nlist_blocks items per replica); evaluations of the
 // replicas with `ng` Gaussians (0: any count, read at run time; 9: FP64 with
@@ -307,7 +316,7 @@ struct FarArgs {
     const int32_t *order;
     const double4 *samp;       // [P] (nx, ny, nz, coef)
     const double2 *gk;         // [P] coef * rho
-    const double *fnear;       // [kNearLanes][3][N] partial near forces of the lanes, cell order
+    const double *fnear;       // [3][N] near forces, cell order
     double *f;                 // null, or SoA [3][N] forces in caller order (through order)
     double *f_near_out;        // null, or SoA [3][N] near forces in caller order
     double *fs;                // null, or SoA [3][N] forces in cell order
