@@ -352,18 +352,24 @@ __device__ inline double readlane_f64(double v, int l)
 // cell of a row of odd length alone) hold the home particles [h_beg, h_end);
 // their candidates are the particles of 25 rows (dz, dy = -2..2) of the cells
 // x0 - 2 .. x1 + 2, each row one contiguous range of the cell order or two
-// where it wraps, 50 pieces at most.  Lane l < 50 describes piece l; the
-// pieces' starts, exclusive prefix sums of their lengths and image-shift codes
-// (0/1/2 for -L/0/+L per axis) go to the wave's rows of pstart/ppref/pcode.
+// where it wraps, 50 pieces at most.  Lane l < 50 describes piece l in the wave's
+// tables.
 // Returns false, uniformly over the wave, when q is past the last pair or the
 // pair has no home particle.  A window holds each particle at most once: it is
 // at most 6 cells wide in x and 5 in y and z, and the grid has at least 6.
+// Positions are taken relative to the pair's centre, so that a distance test
+// can be written out as |c|^2 - 2 h.c + |h|^2 without losing its digits.
 struct PairWindow {
-    int h_beg, h_end, total;
+    int h_beg, h_end, total;   // home particles; candidates (all uniform)
 };
 
-__device__ inline bool pair_window(const NearArgs &a, int q, int32_t *pstart, int32_t *ppref, int32_t *pcode,
-                                   PairWindow &win)
+struct PairTables {            // one wave's window, by piece
+    int32_t pref[64];          // exclusive prefix sums of the pieces' lengths
+    int32_t first[64];         // particle index of candidate c of the piece, less c
+    double shift[3][64];       // image shift less the centre
+};
+
+__device__ inline bool pair_window(const NearArgs &a, int q, PairTables &w, double centre[3], PairWindow &win)
 {
     const int lane = threadIdx.x & 63;
     const int nf = a.g.nc[0], nfy = a.g.nc[1], nfz = a.g.nc[2], half = (nf + 1) >> 1;
@@ -372,19 +378,22 @@ __device__ inline bool pair_window(const NearArgs &a, int q, int32_t *pstart, in
     const int cz = row / nfy, cy = row - cz * nfy;
     const int x0 = 2 * ix, x1 = min(x0 + 1, nf - 1);
     const int cbase = (cz * nfy + cy) * nf;
-    win.h_beg = a.cell_start[cbase + x0];
-    win.h_end = a.cell_start[cbase + x1 + 1];
+    win.h_beg = __builtin_amdgcn_readfirstlane(a.cell_start[cbase + x0]);
+    win.h_end = __builtin_amdgcn_readfirstlane(a.cell_start[cbase + x1 + 1]);
     if (win.h_beg >= win.h_end) return false;
-    int ps = 0, plen = 0, pc = 0;
+    centre[0] = (double)(x0 + 1) * a.w[0];
+    centre[1] = ((double)cy + 0.5) * a.w[1];
+    centre[2] = ((double)cz + 0.5) * a.w[2];
+    int ps = 0, plen = 0, xc = 1, yc = 1, zc = 1;
     if (lane < 2 * 25) {
         const int r = lane >> 1, k = lane & 1;
-        int czw = cz + r / 5 - 2, zc = 1;
+        int czw = cz + r / 5 - 2;
         if (czw < 0) { czw += nfz; zc = 0; } else if (czw >= nfz) { czw -= nfz; zc = 2; }
-        int cyw = cy + r % 5 - 2, yc = 1;
+        int cyw = cy + r % 5 - 2;
         if (cyw < 0) { cyw += nfy; yc = 0; } else if (cyw >= nfy) { cyw -= nfy; yc = 2; }
         const int rb = (czw * nfy + cyw) * nf;
         const int xa = x0 - 2, xb = x1 + 2;   // at most 6 cells <= nf: one side wraps at most
-        int lo = xa, hi = xb, xc = 1;
+        int lo = xa, hi = xb;
         bool has = k == 0;
         if (xa < 0) {
             has = true;
@@ -396,7 +405,6 @@ __device__ inline bool pair_window(const NearArgs &a, int q, int32_t *pstart, in
         if (has) {
             ps = a.cell_start[rb + lo];
             plen = a.cell_start[rb + hi + 1] - ps;
-            pc = xc | (yc << 2) | (zc << 4);
         }
     }
     int incl = plen;
@@ -405,10 +413,12 @@ __device__ inline bool pair_window(const NearArgs &a, int q, int32_t *pstart, in
         int u = __shfl_up(incl, off);
         if (lane >= off) incl += u;
     }
-    win.total = __shfl(incl, 63);
-    pstart[lane] = ps;
-    ppref[lane] = incl - plen;
-    pcode[lane] = pc;
+    win.total = __builtin_amdgcn_readlane(incl, 63);
+    w.pref[lane] = incl - plen;
+    w.first[lane] = ps - (incl - plen);
+    w.shift[0][lane] = shift_of(xc, a.g.L[0]) - centre[0];
+    w.shift[1][lane] = shift_of(yc, a.g.L[1]) - centre[1];
+    w.shift[2][lane] = shift_of(zc, a.g.L[2]) - centre[2];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -439,31 +449,26 @@ __device__ inline int window_piece(const int32_t *ppref, int c)
     return lo - 1;
 }
 
-// Candidate c of piece l of a window: its particle index j and the image shift
-// (sx, sy, sz) the piece is seen under.
-__device__ inline int window_candidate(const int32_t *pstart, const int32_t *ppref, const int32_t *pcode, int c,
-                                       int l, const double Lb[3], double &sx, double &sy, double &sz)
-{
-    const int code = pcode[l];
-    sx = shift_of(code & 3, Lb[0]);
-    sy = shift_of((code >> 2) & 3, Lb[1]);
-    sz = shift_of(code >> 4, Lb[2]);
-    return pstart[l] + (c - ppref[l]);
-}
-
 // One wave lists the neighbours of the home particles of cell pair q,
 // kListHomes of them per pass over the window.  Lanes take 64 consecutive
 // candidates of the window at a time (loads coalesced along the rows); each
 // home particle of the pass, its position read from LDS by every lane (a
 // broadcast), is tested against all 64, and the accepted ones are appended
-// in lane order (ballot / mbcnt) to that particle's list, the pass's running
-// counts staying wave-uniform (scalar registers).  So a particle's list holds
+// in lane order (ballot / mbcnt) to that particle's list.  So a particle's list holds
 // the candidates within the list radius in window order — planes, rows, wrap
 // pieces, cell order — the same list, entry for entry, as a walk of the
 // particle's own 5 x 5 x 5 cells: the pair window's extra cells lie at least
 // 2 w >= r_c + skin away from the other cell's particles.  A particle with
 // more than list_rows(kp) neighbours gets the count list_rows(kp) + 1 (its
 // lanes then walk the cells in the evaluation).
+//
+// Bound by the vector and scalar instructions of its tests (~10 candidates of
+// 64 pass one): a test is three FMAs and a compare (|c|^2 - 2 h.c < R^2 -
+// |h|^2) where the difference took seven instructions, and two homes share the
+// loop control, since the four SIMDs of a compute unit share one scalar unit
+// (with the running counts and the overflow check in scalar registers too, 19
+// scalar instructions a test, the launch took 0.54 ms).  N = 1e6 plasma: 0.44
+// -> 0.37 ms a build, 222 -> 169 M vector instructions.
 constexpr int kListHomes = 16;
 // windows of up to this many candidates get a table of each candidate's piece
 // (one byte each, in LDS), written once per window: a lookup per candidate in
@@ -472,101 +477,117 @@ constexpr int kListHomes = 16;
 constexpr int kPieceTab = 2048;
 static_assert(kListBlock == 8, "a list block is read as two int4");
 
+// The tests of homes hp and hp + 1 of a pass against a chunk of 64 candidates
+// (one per lane: image-shifted position, its square, particle index j), and the
+// appends: the accepted lanes as one wave mask (the test, less the home's own
+// lane: own is the pass's home a lane holds), under which they store at positions by
+// mbcnt from the list's running end.  Appends past the capacity all land on the
+// row's last entry: the list is then marked overflowed and never read.  The
+// homes' data are read from LDS (a broadcast), not held in registers for every
+// home.  Two homes at a time: their LDS reads overlap, and the scalar unit,
+// which the four SIMDs of a compute unit share, has half the loop control.
+__device__ inline void nlist_test(const double4 *home, double px, double py, double pz, double pp, int j, int own,
+                                  int32_t *pass_row, uint32_t rows, int hp, uint32_t *slot)
+{
+    __asm__ volatile("" ::: "memory");
+    const double4 h0 = home[hp], h1 = home[hp + 1];
+    const double t0 = fma(h0.x, px, fma(h0.y, py, fma(h0.z, pz, pp)));
+    const double t1 = fma(h1.x, px, fma(h1.y, py, fma(h1.z, pz, pp)));
+    const uint64_t m[2] = {__builtin_amdgcn_ballot_w64(t0 < h0.w) & __builtin_amdgcn_ballot_w64(own != hp),
+                           __builtin_amdgcn_ballot_w64(t1 < h1.w) & __builtin_amdgcn_ballot_w64(own != hp + 1)};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t last = (uint32_t)(hp + i + 1) * rows - 1u;
+        const uint32_t k = min(__builtin_amdgcn_mbcnt_hi((uint32_t)(m[i] >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m[i], slot[hp + i])), last);
+        if (__builtin_amdgcn_inverse_ballot_w64(m[i])) *(int32_t *)((char *)pass_row + (k << 2)) = j;
+        slot[hp + i] += (uint32_t)__popcll(m[i]);
+    }
+}
+
 __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
 {
-    __shared__ int32_t pstart[kListWaves][64], ppref[kListWaves][64], pcode[kListWaves][64];
-    __shared__ double hpos[kListWaves][3][kListHomes];
+    __shared__ PairTables tabs[kListWaves];
+    __shared__ double4 home[kListWaves][kListHomes];
     __shared__ uint8_t pidx[kListWaves][kPieceTab];
     const int lane = threadIdx.x & 63;
+    PairTables &w = tabs[wv];
     PairWindow win;
-    if (!pair_window(a, q, pstart[wv], ppref[wv], pcode[wv], win)) return;   // uniform per wave
+    double centre[3];
+    if (!pair_window(a, q, w, centre, win)) return;   // uniform per wave
     const int total = win.total;
     const bool tabled = total <= kPieceTab;   // uniform
     if (tabled) {   // lane l writes its piece's index over the piece's candidates
-        const int b0 = ppref[wv][lane], b1 = lane < 63 ? ppref[wv][lane + 1] : total;
+        const int b0 = w.pref[lane], b1 = lane < 63 ? w.pref[lane + 1] : total;
         for (int t = b0; t < b1; ++t) pidx[wv][t] = (uint8_t)lane;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    const int rows = list_rows(a.kp);
+    const uint32_t rows = (uint32_t)list_rows(a.kp);
     // The home particles are consecutive candidates of the window's central
     // row (dy = dz = 0, no image shift): piece 24 of that row, or piece 25
     // when the row wraps at the low x side (its first piece is then the
     // wrapped cells).  home_c is the candidate index of h_beg, so the lane
     // that holds a home itself follows from the lane's candidate index.
-    const int lhome = pair_window_home_piece(a, q);
-    const int home_c = __builtin_amdgcn_readfirstlane(ppref[wv][lhome] + (win.h_beg - pstart[wv][lhome]));
-    // the list radius with a relative margin of 1e-12: a candidate is tested
-    // as home - (its position + image shift), the evaluation forms the same
-    // difference in another order, and a pair on the radius must not be lost
-    // to the rounding (extra pairs beyond r_c are skipped by the evaluation)
-    const double R2 = a.rl2 * (1.0 + 1e-12);
+    const int home_c = win.h_beg - __builtin_amdgcn_readfirstlane(w.first[pair_window_home_piece(a, q)]);
+    // the list radius squared with a relative margin of 1e-12 and the rounding
+    // of an image-shifted position (a few ulp of the box edge): a candidate is
+    // tested in another form than the evaluation's difference, and a pair on
+    // the radius must not be lost to the rounding (extra pairs beyond r_c are
+    // skipped by the evaluation)
+    const double Lmax = fmax(a.g.L[0], fmax(a.g.L[1], a.g.L[2]));
+    const double R2 = a.rl2 * (1.0 + 1e-12) + 0x1p-48 * Lmax * sqrt(a.rl2);
     for (int hb = win.h_beg; hb < win.h_end; hb += kListHomes) {
-        const int nh = min(kListHomes, win.h_end - hb);
-        if (lane < nh) {
-            const double4 r = a.xs[hb + lane];
-            hpos[wv][0][lane] = r.x;
-            hpos[wv][1][lane] = r.y;
-            hpos[wv][2][lane] = r.z;
+        const int nh = min(kListHomes, win.h_end - hb);   // uniform
+        if (lane < kListHomes) {   // |c - h|^2 < R2 as |c|^2 - 2 h.c < R2 - |h|^2; past nh nothing passes
+            double4 h = make_double4(0.0, 0.0, 0.0, -HUGE_VAL);
+            if (lane < nh) {
+                const double4 r = a.xs[hb + lane];
+                const double hx = r.x - centre[0], hy = r.y - centre[1], hz = r.z - centre[2];
+                h = make_double4(-2.0 * hx, -2.0 * hy, -2.0 * hz, R2 - (hx * hx + hy * hy + hz * hz));
+            }
+            home[wv][lane] = h;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         // the pass's homes' lists are consecutive rows from pass_row on; slot[hh]
-        // is the next entry of home hh counted from pass_row (hh rows + count)
-        int32_t *pass_row = a.nbr + list_at(hb, 0, rows);
+        // is the next entry of home hh counted from pass_row (hh rows + count;
+        // a wave-uniform value held in a vector register, where mbcnt adds it)
+        int32_t *pass_row = a.nbr + list_at(hb, 0, (int)rows);
         uint32_t slot[kListHomes];
 #pragma unroll
-        for (int hh = 0; hh < kListHomes; ++hh) slot[hh] = (uint32_t)(hh * rows);
+        for (int hh = 0; hh < kListHomes; ++hh) {
+            slot[hh] = (uint32_t)hh * rows;
+            __asm__("" : "+v"(slot[hh]));
+        }
         const int hc = home_c + (hb - win.h_beg);   // candidate index of the pass's first home
         for (int c0 = 0; c0 < total; c0 += 64) {
             const int c = c0 + lane;
-            const bool live = c < total;
-            const uint64_t live_m = __builtin_amdgcn_ballot_w64(live);
-            const int own = c - hc;   // the pass's home whose own lane this is (any other value: none)
             int j = -1;
-            double px = 0.0, py = 0.0, pz = 0.0;   // the candidate, image-shifted
-            if (live) {
-                double sx, sy, sz;
-                const int l = tabled ? (int)pidx[wv][c] : window_piece(ppref[wv], c);
-                j = window_candidate(pstart[wv], ppref[wv], pcode[wv], c, l, a.g.L, sx, sy, sz);
+            double px = 0.0, py = 0.0, pz = 0.0, pp = HUGE_VAL;   // the candidate, image-shifted; none past the last
+            if (c < total) {
+                const int l = tabled ? (int)pidx[wv][c] : window_piece(w.pref, c);
+                j = w.first[l] + c;
                 const double4 qj = a.xs[j];
-                px = qj.x + sx;
-                py = qj.y + sy;
-                pz = qj.z + sz;
+                px = qj.x + w.shift[0][l];
+                py = qj.y + w.shift[1][l];
+                pz = qj.z + w.shift[2][l];
+                pp = px * px + py * py + pz * pz;
             }
+            const int own = c - hc;   // the pass's home whose own lane this is (any other value: none)
 #pragma unroll
-            for (int hh = 0; hh < kListHomes; ++hh) {
-                if (hh < nh) {   // uniform
-                    // the home's position is read from LDS at each test (a
-                    // broadcast), not held in registers for every home
-                    __asm__ volatile("" ::: "memory");
-                    const double dx = hpos[wv][0][hh] - px, dy = hpos[wv][1][hh] - py, dz = hpos[wv][2][hh] - pz;
-                    // the accepted lanes as one wave mask (the distance test,
-                    // the live lanes, not the home's own lane); the appends
-                    // run under it, at positions by mbcnt.  Appends past the
-                    // capacity all land on the row's last entry: the list is
-                    // then marked overflowed and never read.
-                    const uint64_t m = __builtin_amdgcn_ballot_w64(dx * dx + dy * dy + dz * dz < R2) & live_m &
-                                       __builtin_amdgcn_ballot_w64(own != hh);
-                    if (__builtin_amdgcn_inverse_ballot_w64(m)) {
-                        const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, slot[hh]));
-                        const uint32_t kk = min(k, (uint32_t)(hh * rows + rows - 1));
-                        *(int32_t *)((char *)pass_row + (kk << 2)) = j;
-                    }
-                    slot[hh] += (uint32_t)__popcll(m);
-                }
-            }
+            for (int hp = 0; hp < kListHomes; hp += 2)
+                if (hp < nh) nlist_test(home[wv], px, py, pz, pp, j, own, pass_row, rows, hp, slot);   // uniform
         }
-        int mine = 0;
+        uint32_t mine = 0;
 #pragma unroll
         for (int hh = 0; hh < kListHomes; ++hh)
-            if (lane == hh) mine = (int)(slot[hh] - (uint32_t)(hh * rows));
+            if (lane == hh) mine = slot[hh] - (uint32_t)hh * rows;
         if (lane < nh) {
-            a.nbr_cnt[hb + lane] = mine > rows ? rows + 1 : mine;
-            if (mine == 0) pass_row[(size_t)lane * rows] = hb + lane;   // entry 0 is always a valid index
+            a.nbr_cnt[hb + lane] = (int)(mine > rows ? rows + 1u : mine);
+            if (mine == 0) pass_row[(uint32_t)lane * rows] = hb + lane;   // entry 0 is always a valid index
         }
         // the positions of the next pass overwrite these
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -578,7 +599,7 @@ __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
 __device__ inline void nlist_body(const NearArgs &a, int lb)
 {
     if (a.gate && *a.gate == 0) return;
-    const int wv = threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     nlist_pair(a, lb * kListWaves + wv, wv);
 }
 
