@@ -156,23 +156,32 @@ constexpr SinCosShort make_sincos_short()
 // (sin, cos)(2 pi j / 128): w = m + f exactly with m = rint(w) and |f| <= 1/2
 // (for |w| < 2^52 the difference is exact), the short series give the rotation
 // by f and the table entry of m mod 128 (in LDS) the rest.
-__device__ inline void sincos_rev_tab(double w, const double2 *tab, const SinCosShort &P, double *s, double *c)
+// (rotation_tab: the entry and the rotation's sine and cosine by themselves.)
+__device__ inline void rotation_tab(double w, const double2 *tab, const SinCosShort &P, double2 *t, double *sp,
+                                    double *cp)
 {
     double jr = rint(w);
     double f = w - jr;
-    double2 t = tab[(int)jr & (kPhaseTab - 1)];
+    *t = tab[(int)jr & (kPhaseTab - 1)];
     double f2 = f * f;
-    double sp = fma(fma(fma(P.s[3], f2, P.s[2]), f2, P.s[1]), f2, P.s[0]) * f;
-    double cp = fma(fma(fma(P.c[3], f2, P.c[2]), f2, P.c[1]), f2, P.c[0]);
+    *sp = fma(fma(fma(P.s[3], f2, P.s[2]), f2, P.s[1]), f2, P.s[0]) * f;
+    *cp = fma(fma(fma(P.c[3], f2, P.c[2]), f2, P.c[1]), f2, P.c[0]);
+}
+
+__device__ inline void sincos_rev_tab(double w, const double2 *tab, const SinCosShort &P, double *s, double *c)
+{
+    double2 t;
+    double sp, cp;
+    rotation_tab(w, tab, P, &t, &sp, &cp);
     *s = fma(t.x, cp, t.y * sp);
     *c = fma(t.y, cp, -(t.x * sp));
 }
 
-// The far field's finer table: 1024 entries (16 KB of LDS, which only the far
-// kernel carries), so that the remainder |f| <= 1/2 in 1/1024 revolutions is
-// at most pi/1024 rad and degree-5/4 series suffice (first omitted terms below
-// 6e-22 relative to sin and 2e-18 absolute for cos): two FMA fewer per
-// (particle, mode) than the 128-entry form.
+// The finer table of the far field and of a step's structure-factor partials:
+// 1024 entries (16 KB of LDS), so that the remainder |f| <= 1/2 in 1/1024
+// revolutions is at most pi/1024 rad and degree-5/4 series suffice (first
+// omitted terms below 6e-22 relative to sin and 2e-18 absolute for cos): two FMA
+// fewer per (particle, mode) than the 128-entry form.
 constexpr int kFarTab = 1024;
 struct SinCosFar {
     double s[3];
@@ -190,20 +199,28 @@ constexpr SinCosFar make_sincos_far()
 }
 
 // sin and cos of 2 pi w / 1024 for a phase w in 1/1024 revolutions, as
-// sincos_rev_tab with the far field's table
-__device__ inline void sincos_rev_far(double w, const double2 *tab, const SinCosFar &P, double *s, double *c)
+// sincos_rev_tab with the finer table
+__device__ inline void rotation_far(double w, const double2 *tab, const SinCosFar &P, double2 *t, double *sp,
+                                    double *cp)
 {
     double jr = rint(w);
     double f = w - jr;
-    double2 t = tab[(int)jr & (kFarTab - 1)];
+    *t = tab[(int)jr & (kFarTab - 1)];
     double f2 = f * f;
-    double sp = fma(fma(P.s[2], f2, P.s[1]), f2, P.s[0]) * f;
-    double cp = fma(fma(P.c[2], f2, P.c[1]), f2, P.c[0]);
+    *sp = fma(fma(P.s[2], f2, P.s[1]), f2, P.s[0]) * f;
+    *cp = fma(fma(P.c[2], f2, P.c[1]), f2, P.c[0]);
+}
+
+__device__ inline void sincos_rev_far(double w, const double2 *tab, const SinCosFar &P, double *s, double *c)
+{
+    double2 t;
+    double sp, cp;
+    rotation_far(w, tab, P, &t, &sp, &cp);
     *s = fma(t.x, cp, t.y * sp);
     *c = fma(t.y, cp, -(t.x * sp));
 }
 
-// The same in FP32 after the exact FP64 reduction to [-1/2, 1/2] revolutions:
+// Sine and cosine in FP32 after the exact FP64 reduction to [-1/2, 1/2] revolutions:
 // the hardware sine and cosine take their argument in revolutions.
 __device__ inline void sincos_rev_f32(double u, float *s, float *c)
 {

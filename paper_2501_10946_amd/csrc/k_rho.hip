@@ -127,10 +127,10 @@ __global__ __launch_bounds__(kBlock) void k_rho_full(RhoArgs a)
         const int nj = min(kBlock, a.N - j0);
         int i = 0;
         for (; i + 1 < nj; i += 2) {
-            rho_term<true, MIXED>(a, tab, k, sp[i], re0, im0);
-            rho_term<true, MIXED>(a, tab, k, sp[i + 1], re1, im1);
+            rho_term<MIXED>(a, tab, k, sp[i], re0, im0);
+            rho_term<MIXED>(a, tab, k, sp[i + 1], re1, im1);
         }
-        if (i < nj) rho_term<true, MIXED>(a, tab, k, sp[i], re0, im0);
+        if (i < nj) rho_term<MIXED>(a, tab, k, sp[i], re0, im0);
     }
     if (live) {
         const double re = re0 + re1, im = im0 + im1, cf = k.w;
