@@ -429,8 +429,7 @@ FarArgs far_args(rbsog_handle *h, const double4 *samp, double *f, double *f_near
     fa.kepart = kick ? h->kepart : nullptr;
     fa.flag = h->flag;
     fa.mixed = h->p.precision == RBSOG_MIXED;
-    fa.tab = h->tab_far;
-    fa.ss = make_sincos_far();
+    fa.ss = make_sin_poly();
     return fa;
 }
 

@@ -248,6 +248,15 @@ __device__ inline double mode_vm(const RhoArgs &a, const double4 &sl)
     return F > 0.0 ? k2 * G / F : 0.0;
 }
 
+// What the far field takes of a mode's weight cf and structure factor: cf rho
+// (mixed), or its size and the phase offset with which Im(exp(-i k.r) cf rho) =
+// size cos(2 pi (k.r/(2 pi) + offset)), offset = 1/4 - arg(rho)/(2 pi) (FP64).
+__device__ inline double2 far_coef(int mixed, double cf, double re, double im)
+{
+    if (mixed) return make_double2(cf * re, cf * im);
+    return make_double2(cf * sqrt(re * re + im * im), 0.25 - atan2(im, re) * 0.15915494309189535);
+}
+
 // Fixed-order sum of the chunk partials, one workgroup per kRedModes adjacent
 // samples so that each partial row is read as one contiguous segment.  Thread
 // t takes sample l = kRedModes b + (t mod kRedModes) and adds the partials of
@@ -300,7 +309,7 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
         }
         double cf = a.samp[l].w;
         a.rho[l] = make_double2(re, im);
-        a.gk[l] = make_double2(cf * re, cf * im);
+        a.gk[l] = far_coef(a.mixed, cf, re, im);
         a.eF[l] = 0.5 * cf * (re * re + im * im);
         if (a.eW) a.eW[l] = cf * (re * re + im * im) * (1.5 - mode_vm(a, a.samp[l]));
         if (a.rho_out) {

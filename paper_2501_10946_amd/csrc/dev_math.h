@@ -177,11 +177,11 @@ __device__ inline void sincos_rev_tab(double w, const double2 *tab, const SinCos
     *c = fma(t.y, cp, -(t.x * sp));
 }
 
-// The finer table of the far field and of a step's structure-factor partials:
-// 1024 entries (16 KB of LDS), so that the remainder |f| <= 1/2 in 1/1024
-// revolutions is at most pi/1024 rad and degree-5/4 series suffice (first
-// omitted terms below 6e-22 relative to sin and 2e-18 absolute for cos): two FMA
-// fewer per (particle, mode) than the 128-entry form.
+// The finer table of a step's structure-factor partials: 1024 entries (16 KB of
+// LDS), so that the remainder |f| <= 1/2 in 1/1024 revolutions is at most
+// pi/1024 rad and degree-5/4 series suffice (first omitted terms below 6e-22
+// relative to sin and 2e-18 absolute for cos): two FMA fewer per (particle,
+// mode) than the 128-entry form.
 constexpr int kFarTab = 1024;
 struct SinCosFar {
     double s[3];
@@ -218,6 +218,35 @@ __device__ inline void sincos_rev_far(double w, const double2 *tab, const SinCos
     rotation_far(w, tab, P, &t, &sp, &cp);
     *s = fma(t.x, cp, t.y * sp);
     *c = fma(t.y, cp, -(t.x * sp));
+}
+
+// The far field needs one real number per (particle, mode), the cosine of the
+// phase measured from the structure factor's own: no table (nor the LDS reads
+// and bank conflicts of one), one polynomial.  -cos(2 pi w) for w in
+// revolutions: with r = w - rint(w) in [-1/2, 1/2] and b = |r| - 1/4, cos(2 pi w)
+// = cos(2 pi |r|) = -sin(2 pi b), |2 pi b| <= pi/2, by the degree-17 odd
+// polynomial of gen_sin_poly.py (within 3.2e-17 of the sine).  13 instructions
+// against 17 of the two rotated table values and their product with the
+// structure factor.
+struct SinPoly {
+    double s[9];
+};
+constexpr SinPoly make_sin_poly()
+{
+    return SinPoly{{0x1.921fb54442d18p+2, -0x1.4abbce625be52p+5, 0x1.466bc6775aa7dp+6, -0x1.32d2cce627c86p+6,
+                    0x1.5078348551854p+5, -0x1.e3074dfaf87afp+3, 0x1.e8f3675ee37ddp+1, -0x1.6f7acdb8f6580p-1,
+                    0x1.9d462020fcc78p-4}};
+}
+
+__device__ inline double neg_cos_rev(double w, const SinPoly &P)
+{
+    const double r = w - rint(w);
+    const double b = fabs(r) - 0.25;
+    const double z = b * b;
+    double p = P.s[8];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) p = fma(p, z, P.s[k]);
+    return p * b;
 }
 
 // Sine and cosine in FP32 after the exact FP64 reduction to [-1/2, 1/2] revolutions:

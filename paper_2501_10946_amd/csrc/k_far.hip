@@ -8,118 +8,144 @@ namespace rbsog {
 // ---------------------------------------------------------------------------
 // far field of the random batch (eq. UF):
 //   f_i += -q_i (2 pi / L) sum_l coef_l n_l Im(exp(-i k_l . r_i) rho_l).
-// A workgroup owns 64 consecutive particles (cell order) and has 4 waves; wave
-// g takes the samples l = g mod 4 of each LDS tile of 256 samples, so every
-// particle's sum is spread over 4 lanes (4x the waves of one lane per particle,
-// which the latency of the dependent FP64 chains needs).  The 4 partial sums are
-// added in a fixed order, then near + far is written (in cell order, and/or
-// in the caller's order) and the second half-kick applied in cell order; in a
-// run of steps the next step's first half-kick and drift follow at once.
+// A workgroup owns 64 consecutive particles (cell order), or 128 (PPL particles
+// per lane), and has 4 waves; wave g takes the samples l = g mod 4 of each LDS
+// tile of 256 samples, so every particle's sum is spread over 4 lanes.  The 4
+// partial sums are added in a fixed order, then near + far is written (in cell
+// order, and/or in the caller's order) and the second half-kick applied in cell
+// order; in a run of steps the next step's first half-kick and drift follow at
+// once.  Two particles per lane share the LDS reads of a mode (bound beside the
+// arithmetic otherwise) and give each wave two independent chains more; a
+// system whose workgroups would then fill the chip less than a few times over
+// keeps one.
+//
+// Bound by its vector instructions, 20 per (particle, mode) in FP64: three FMAs of
+// the phase (which start from the mode's offset), 13 of the cosine, three to
+// accumulate.  The table form (sine and cosine from a 1024-entry rotation table,
+// then their product with rho) took 26 and two more LDS reads: N = 1e6, P = 500,
+// 416 us against 323 (1.6e12 (particle, mode) terms a second).  FP64 matrix
+// instructions do not help: the phases as a 16 x 16 x 4 product (72 cycles for 256
+// terms) and the accumulation as 4 x 4 x 4 products (18 cycles for 64) hold up
+// the FP64 vector unit for as long as the FMAs they replace.
 // ---------------------------------------------------------------------------
 
 constexpr int kFarGroups = 4;
 constexpr int kFarThreads = 64 * kFarGroups;
 constexpr int kFarTile = 256;
 
-// Im(exp(-i k.r) coef rho) of one mode (kv: n, gv: coef rho); (sx, sy, sz) is
-// r/L (mixed) or 1024 r/L (FP64), so that n.s is the phase in the unit that the
-// precision's sine and cosine take.
+// A tile's samples in LDS: k = (n, phase offset) and w = -size n (FP64), or k =
+// (n, coef) and w.xy = coef rho (mixed).
+struct FarTile {
+    double4 k[kFarTile];
+    double2 w[kFarTile];
+    double wz[kFarTile];
+};
+
+// Adds one mode to a particle's sum; (sx, sy, sz) is r/L, so that n.s is the
+// phase in revolutions.
 template <bool MIXED>
-__device__ inline double far_term(const FarArgs &a, const double2 *tab, const double4 &kv, const double2 &gv,
-                                  double sx, double sy, double sz)
+__device__ inline void far_add(const FarArgs &a, const double4 &k, const double2 &w, double wz, const double s[3],
+                               double acc[3])
 {
-    double u = kv.x * sx + kv.y * sy + kv.z * sz;
     if (MIXED) {
+        const double u = k.x * s[0] + k.y * s[1] + k.z * s[2];
         float sn, cs;
         sincos_rev_f32(u, &sn, &cs);
-        return gv.y * (double)cs - gv.x * (double)sn;
+        const double im = w.y * (double)cs - w.x * (double)sn;
+        acc[0] += im * k.x;
+        acc[1] += im * k.y;
+        acc[2] += im * k.z;
     } else {
-        double sn, cs;
-        sincos_rev_far(u, tab, a.ss, &sn, &cs);
-        return gv.y * cs - gv.x * sn;
+        const double c = neg_cos_rev(fma(k.x, s[0], fma(k.y, s[1], fma(k.z, s[2], k.w))), a.ss);
+        acc[0] = fma(c, w.x, acc[0]);
+        acc[1] = fma(c, w.y, acc[1]);
+        acc[2] = fma(c, wz, acc[2]);
     }
 }
 
-template <bool MIXED, bool DRIFT>
+template <bool MIXED, bool DRIFT, int PPL>
 __device__ inline void far_body(const FarArgs &a, int b)
 {
-    __shared__ double4 sk[kFarTile];
-    __shared__ double2 sg[kFarTile];
-    __shared__ double2 tab[kFarTab];
-    __shared__ double red[64];
-    static_assert(sizeof(sk) >= 3 * kFarThreads * sizeof(double), "partials reuse the sample tile");
-    double(*part)[kFarThreads] = (double(*)[kFarThreads])sk;
+    __shared__ FarTile tile;
+    static_assert(sizeof(tile) >= 3 * PPL * kFarThreads * sizeof(double), "partials reuse the sample tile");
+    double(*part)[PPL * kFarThreads] = (double(*)[PPL * kFarThreads])&tile;
     const int t = threadIdx.x;
     const int g = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;   // g is uniform per wave
-    const int p = b * 64 + lane;
     if (a.gate_clear && b == 0 && t == 0) {
         if (a.rebuilds && *a.gate_clear) *a.rebuilds += 1;
         *a.gate_clear = 0;
     }
-    const bool live = p < a.N;
-    double4 pi = live ? a.xs[p] : make_double4(0.0, 0.0, 0.0, 0.0);
-    // phases in revolutions (mixed) or 1/1024 revolutions (FP64 table path)
-    const double phx = MIXED ? a.inv_L[0] : a.inv_L[0] * kFarTab;
-    const double phy = MIXED ? a.inv_L[1] : a.inv_L[1] * kFarTab;
-    const double phz = MIXED ? a.inv_L[2] : a.inv_L[2] * kFarTab;
-    double sx = pi.x * phx, sy = pi.y * phy, sz = pi.z * phz;
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    if (!MIXED)
-        for (int k = t; k < kFarTab; k += kFarThreads) tab[k] = a.tab[k];
+    double s[PPL][3], acc[PPL][3];
+#pragma unroll
+    for (int i = 0; i < PPL; ++i) {
+        const int p = (b * PPL + i) * 64 + lane;
+        const double4 pi = p < a.N ? a.xs[p] : make_double4(0.0, 0.0, 0.0, 0.0);
+        s[i][0] = pi.x * a.inv_L[0];
+        s[i][1] = pi.y * a.inv_L[1];
+        s[i][2] = pi.z * a.inv_L[2];
+        acc[i][0] = acc[i][1] = acc[i][2] = 0.0;
+    }
     for (int l0 = 0; l0 < a.P; l0 += kFarTile) {
         __syncthreads();
         if (l0 + t < a.P) {
-            sk[t] = a.samp[l0 + t];
-            sg[t] = a.gk[l0 + t];
+            const double4 k = a.samp[l0 + t];
+            const double2 gk = a.gk[l0 + t];
+            if (MIXED) {
+                tile.k[t] = k;
+                tile.w[t] = gk;
+            } else {
+                tile.k[t] = make_double4(k.x, k.y, k.z, gk.y);
+                tile.w[t] = make_double2(-gk.x * k.x, -gk.x * k.y);
+                tile.wz[t] = -gk.x * k.z;
+            }
         }
         __syncthreads();
         int nl = min(kFarTile, a.P - l0);
         // two modes per pass (independent chains), added in mode order
-        int k = g;
-        for (; k + kFarGroups < nl; k += 2 * kFarGroups) {
-            const double4 k0 = sk[k], k1 = sk[k + kFarGroups];
-            const double im0 = far_term<MIXED>(a, tab, k0, sg[k], sx, sy, sz);
-            const double im1 = far_term<MIXED>(a, tab, k1, sg[k + kFarGroups], sx, sy, sz);
-            ax += im0 * k0.x;
-            ay += im0 * k0.y;
-            az += im0 * k0.z;
-            ax += im1 * k1.x;
-            ay += im1 * k1.y;
-            az += im1 * k1.z;
+        int m = g;
+        for (; m + kFarGroups < nl; m += 2 * kFarGroups) {
+            const double4 k0 = tile.k[m], k1 = tile.k[m + kFarGroups];
+            const double2 w0 = tile.w[m], w1 = tile.w[m + kFarGroups];
+            const double z0 = MIXED ? 0.0 : tile.wz[m], z1 = MIXED ? 0.0 : tile.wz[m + kFarGroups];
+#pragma unroll
+            for (int i = 0; i < PPL; ++i) {
+                far_add<MIXED>(a, k0, w0, z0, s[i], acc[i]);
+                far_add<MIXED>(a, k1, w1, z1, s[i], acc[i]);
+            }
         }
-        if (k < nl) {
-            const double4 k0 = sk[k];
-            const double im0 = far_term<MIXED>(a, tab, k0, sg[k], sx, sy, sz);
-            ax += im0 * k0.x;
-            ay += im0 * k0.y;
-            az += im0 * k0.z;
+        if (m < nl) {
+            const double4 k0 = tile.k[m];
+            const double2 w0 = tile.w[m];
+            const double z0 = MIXED ? 0.0 : tile.wz[m];
+#pragma unroll
+            for (int i = 0; i < PPL; ++i) far_add<MIXED>(a, k0, w0, z0, s[i], acc[i]);
         }
     }
     __syncthreads();   // the sample tile is done with: it holds the partials next
-    part[0][t] = ax;
-    part[1][t] = ay;
-    part[2][t] = az;
+#pragma unroll
+    for (int i = 0; i < PPL; ++i) {
+        const int at = (g * PPL + i) * 64 + lane;   // group g's partial of particle (i, lane)
+        part[0][at] = acc[i][0];
+        part[1][at] = acc[i][1];
+        part[2][at] = acc[i][2];
+    }
     __syncthreads();
+    if (t >= 64 * PPL) return;   // whole waves; thread t finishes particle t
+    const int p = b * PPL * 64 + t;
     double ke = 0.0;
-    if (t < 64 && live) {
+    if (p < a.N) {
+        const double4 pi = a.xs[p];
         double bx = 0.0, by = 0.0, bz = 0.0;
 #pragma unroll
         for (int k = 0; k < kFarGroups; ++k) {
-            bx += part[0][k * 64 + t];
-            by += part[1][k * 64 + t];
-            bz += part[2][k * 64 + t];
+            bx += part[0][k * 64 * PPL + t];
+            by += part[1][k * 64 * PPL + t];
+            bz += part[2][k * 64 * PPL + t];
         }
         const double scx = -pi.w * a.two_pi_over_L[0], scy = -pi.w * a.two_pi_over_L[1];
         const double scz = -pi.w * a.two_pi_over_L[2];
-        // near field: the lane partials, added in lane order
-        double fnx = 0.0, fny = 0.0, fnz = 0.0;
-#pragma unroll
-        for (int k = 0; k < kNearLanes; ++k) {
-            const double *pl = a.fnear + (size_t)k * 3 * a.N + p;
-            fnx += pl[0];
-            fny += pl[a.N];
-            fnz += pl[2 * (size_t)a.N];
-        }
+        static_assert(kNearLanes == 1, "one partial near force per particle");
+        const double fnx = a.fnear[p], fny = a.fnear[a.N + p], fnz = a.fnear[2 * (size_t)a.N + p];
         double fx = fnx + scx * bx, fy = fny + scy * by, fz = fnz + scz * bz;
         if (a.fs) {
             a.fs[p] = fx;
@@ -163,21 +189,17 @@ __device__ inline void far_body(const FarArgs &a, int b)
             a.vs[2 * a.N + p] = vz;
         }
     }
-    if (a.kepart) {
-        if (t < 64) red[t] = ke;
-        __syncthreads();
-        for (int off = 32; off > 0; off >>= 1) {
-            if (t < off) red[t] += red[t + off];
-            __syncthreads();
-        }
-        if (t == 0) a.kepart[b] = red[0];
+    if (a.kepart) {   // one partial per 64 particles: a fixed tree over the wave
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) ke += __shfl_down(ke, off);
+        if (lane == 0 && b * PPL + g < far_blocks(a.N)) a.kepart[b * PPL + g] = ke;
     }
 }
 
-template <bool MIXED, bool DRIFT>
+template <bool MIXED, bool DRIFT, int PPL>
 __global__ __launch_bounds__(kFarThreads) void k_far(FarArgs a)
 {
-    far_body<MIXED, DRIFT>(a, (int)blockIdx.x);
+    far_body<MIXED, DRIFT, PPL>(a, (int)blockIdx.x);
 }
 
 template <bool MIXED>
@@ -185,7 +207,7 @@ __global__ __launch_bounds__(kFarThreads) void k_far_batch(const FarArgs *__rest
                                                            const EnsItem *__restrict__ items)
 {
     const EnsItem e = items[blockIdx.x];
-    far_body<MIXED, false>(tab[e.r], e.b);
+    far_body<MIXED, false, 1>(tab[e.r], e.b);
 }
 
 hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, hipStream_t st)
@@ -196,19 +218,25 @@ hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, boo
     return hipGetLastError();
 }
 
+template <bool MIXED, bool DRIFT>
+static void launch_far_as(const FarArgs &a, hipStream_t st)
+{
+    const int nb = far_blocks(a.N);
+    if (a.N >= kFarPairN) hipLaunchKernelGGL((k_far<MIXED, DRIFT, 2>), dim3((nb + 1) / 2), dim3(kFarThreads), 0, st, a);
+    else hipLaunchKernelGGL((k_far<MIXED, DRIFT, 1>), dim3(nb), dim3(kFarThreads), 0, st, a);
+}
+
 hipError_t launch_far(const FarArgs &a, hipStream_t st)
 {
     if (a.N < 1 || a.P < 1 || !a.xs || !a.order || !a.samp || !a.gk || !a.fnear || (!a.f && !a.fs) || !a.flag ||
-        (a.vs && (!a.ms || !a.kepart)) || (!a.mixed && !a.tab) ||
-        (a.drift && (!a.vs || !a.xb || !a.xs_next || !a.gate_raise)))
+        (a.vs && (!a.ms || !a.kepart)) || (a.drift && (!a.vs || !a.xb || !a.xs_next || !a.gate_raise)))
         return hipErrorInvalidValue;
-    dim3 grid(far_blocks(a.N));
     if (a.drift) {
-        if (a.mixed) hipLaunchKernelGGL((k_far<true, true>), grid, dim3(kFarThreads), 0, st, a);
-        else hipLaunchKernelGGL((k_far<false, true>), grid, dim3(kFarThreads), 0, st, a);
+        if (a.mixed) launch_far_as<true, true>(a, st);
+        else launch_far_as<false, true>(a, st);
     } else {
-        if (a.mixed) hipLaunchKernelGGL((k_far<true, false>), grid, dim3(kFarThreads), 0, st, a);
-        else hipLaunchKernelGGL((k_far<false, false>), grid, dim3(kFarThreads), 0, st, a);
+        if (a.mixed) launch_far_as<true, false>(a, st);
+        else launch_far_as<false, false>(a, st);
     }
     return hipGetLastError();
 }

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kBlock) void k_rho_full(RhoArgs a)
     if (live) {
         const double re = re0 + re1, im = im0 + im1, cf = k.w;
         a.rho[l] = make_double2(re, im);
-        a.gk[l] = make_double2(cf * re, cf * im);
+        a.gk[l] = far_coef(a.mixed, cf, re, im);
         a.eF[l] = 0.5 * cf * (re * re + im * im);
         if (a.eW) a.eW[l] = cf * (re * re + im * im) * (1.5 - mode_vm(a, k));
         if (a.rho_out) {

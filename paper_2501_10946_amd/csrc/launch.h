@@ -195,7 +195,7 @@ struct RhoArgs {
     const double4 *samp;       // [P]
     double2 *part;             // [nchunk][P] partial sums per (group, sample)
     double2 *rho;              // [P]
-    double2 *gk;               // [P] coef * rho
+    double2 *gk;               // [P] far-field coefficients (far_coef)
     double *eF;                // [P] coef |rho|^2 / 2
     double *eW;                // null, or [P] coef |rho|^2 (3/2 - vm): the modes' far-field virial terms
     const double *vm;          // [m_max + 1] vm = k^2 G / Fhat by |n|^2 (a cube, when eW)
@@ -315,7 +315,7 @@ struct FarArgs {
     const double4 *xs;         // cell order
     const int32_t *order;
     const double4 *samp;       // [P] (nx, ny, nz, coef)
-    const double2 *gk;         // [P] coef * rho
+    const double2 *gk;         // [P] the modes' far coefficients (far_coef): coef * rho, or (FP64) its size and phase
     const double *fnear;       // [3][N] near forces, cell order
     double *f;                 // null, or SoA [3][N] forces in caller order (through order)
     double *f_near_out;        // null, or SoA [3][N] near forces in caller order
@@ -326,8 +326,8 @@ struct FarArgs {
     double *kepart;            // [far_blocks(N)] kinetic-energy partials (when vs)
     int *flag;                 // set to 1 on a non-finite force
     int mixed;
-    const double2 *tab;        // [kFarTab] (sin, cos)(2 pi j / kFarTab) (FP64 path)
-    SinCosFar ss;
+    const double2 *tab;        // not read: the FP64 phases take a polynomial (ss)
+    SinPoly ss;
     int32_t *gate_clear;       // null, or a rebuild gate to clear (nothing later in the step reads it)
     int32_t *rebuilds;         // null, or a count of the steps whose gate was raised (with gate_clear)
     // With drift != 0 the kernel also applies the next step's first half-kick
@@ -342,6 +342,11 @@ struct FarArgs {
     int32_t *gate_raise;
     Thermo th;                 // the drift's thermostat (single systems)
 };
+// systems of at least kFarPairN particles: two particles per lane.  N = 3e5: 571
+// us an evaluation with one per lane, 603 with two (2 344 workgroups of which the
+// chip holds ~1 800: a second round that is nearly empty); 4e5: 757 and 768; 5e5:
+// 940 and 926; 1e6: 1 538 and 1 508 us a step.
+constexpr int kFarPairN = 450000;
 hipError_t launch_far(const FarArgs &a, hipStream_t st);
 // ensemble: far_blocks items per replica
 hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, hipStream_t st);
