@@ -269,6 +269,7 @@ CellArgs cell_args(rbsog_handle *h, const CellGeom &g, const int32_t *gate, bool
     a.tile_sum = h->tile_sum;
     a.ticket = h->ticket;
     a.gate = gate;
+    a.rare = gate && h->d.skin > 0.0;
     return a;
 }
 

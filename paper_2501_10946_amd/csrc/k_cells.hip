@@ -58,6 +58,21 @@ __device__ inline int add_runs(int32_t *cnt, int id, bool live, bool want_base)
     return __shfl(base, start) + (lane - start);
 }
 
+// A particle's row as it moves.
+struct CellRow {
+    double4 x;
+    double m, v[3];
+    int32_t order;
+};
+
+__device__ inline int cell_of(const CellGeom &g, const double4 &r)
+{
+    const int cx = cell_coord(r.x, g.inv_cell[0], g.nc[0]);
+    const int cy = cell_coord(r.y, g.inv_cell[1], g.nc[1]);
+    const int cz = cell_coord(r.z, g.inv_cell[2], g.nc[2]);
+    return (cz * g.nc[1] + cy) * g.nc[0] + cx;
+}
+
 // Snapshot of row p for the rank pass and its cell id (stored).
 __device__ inline int cell_id_of(const CellArgs &a, int p)
 {
@@ -69,10 +84,7 @@ __device__ inline int cell_id_of(const CellArgs &a, int p)
     a.ms_old[p] = a.ms[p];
     if (a.vs)
         for (int d = 0; d < 3; ++d) a.vs_old[d * a.N + p] = a.vs[d * a.N + p];
-    int cx = cell_coord(r.x, a.g.inv_cell[0], a.g.nc[0]);
-    int cy = cell_coord(r.y, a.g.inv_cell[1], a.g.nc[1]);
-    int cz = cell_coord(r.z, a.g.inv_cell[2], a.g.nc[2]);
-    int id = (cz * a.g.nc[1] + cy) * a.g.nc[0] + cx;
+    const int id = cell_of(a.g, r);
     a.cell_id[p] = id;
     return id;
 }
@@ -181,11 +193,35 @@ __device__ inline void scatter_body(const CellArgs &a, int b)
     if (live) a.tmp[a.cell_start[c] + slot] = a.order_old[p];
 }
 
+// Row p of the snapshot.
+__device__ inline CellRow old_row(const CellArgs &a, int p)
+{
+    CellRow r;
+    r.x = a.xs_old[p];
+    r.order = a.order_old[p];
+    r.m = a.ms_old[p];
+    if (a.vs)
+        for (int d = 0; d < 3; ++d) r.v[d] = a.vs_old[d * a.N + p];
+    return r;
+}
+
+// A row to position pn of the new order; records the positions of the build.
+__device__ inline void place_row(const CellArgs &a, const CellRow &r, int pn)
+{
+    a.xs[pn] = r.x;
+    a.order[pn] = r.order;
+    a.ms[pn] = r.m;
+    a.xb[pn] = r.x.x;
+    a.xb[a.N + pn] = r.x.y;
+    a.xb[2 * a.N + pn] = r.x.z;
+    if (a.vs)
+        for (int d = 0; d < 3; ++d) a.vs[d * a.N + pn] = r.v[d];
+}
+
 // Stable position: a particle's rank within its cell is the number of cell
 // members with a smaller caller index, so the new order is that of (cell,
 // caller index) whatever order the scatter produced and whatever the old cell
-// order was.  Moves the row, its velocity and mass, and records the positions
-// of the build.
+// order was.
 __device__ inline void rank_body(const CellArgs &a, int b)
 {
     if (!gate_open(a.gate)) return;
@@ -196,16 +232,7 @@ __device__ inline void rank_body(const CellArgs &a, int b)
     int cb = a.cell_start[c], ce = a.cell_start[c + 1];
     int r = 0;
     for (int k = cb; k < ce; ++k) r += (a.tmp[k] < key);
-    const int pn = cb + r;
-    const double4 row = a.xs_old[p];
-    a.xs[pn] = row;
-    a.order[pn] = key;
-    a.ms[pn] = a.ms_old[p];
-    a.xb[pn] = row.x;
-    a.xb[a.N + pn] = row.y;
-    a.xb[2 * a.N + pn] = row.z;
-    if (a.vs)
-        for (int d = 0; d < 3; ++d) a.vs[d * a.N + pn] = a.vs_old[d * a.N + p];
+    place_row(a, old_row(a, p), cb + r);
 }
 
 RBSOG_KERNELS(cell_ids, CellArgs, kBlock)
@@ -213,6 +240,97 @@ RBSOG_KERNELS(scan_tiles, CellArgs, kBlock)
 RBSOG_KERNELS(scan_apply, CellArgs, kBlock)
 RBSOG_KERNELS(scatter, CellArgs, kBlock)
 RBSOG_KERNELS(rank, CellArgs, kBlock)
+
+// ---------------------------------------------------------------------------
+// the whole build of a small system in one workgroup: counts, their scan, the
+// members of each cell and the ranks in LDS; the result is that of the passes
+// above (the same stable order).  A small system's step is a chain of short
+// launches that the host enqueues no faster than the GPU runs them (3.4 us
+// each): with its gate closed this is one of them instead of five (N = 1000: a
+// step 39 -> 28 us).  A build itself is bound by what one compute unit moves:
+// up to four rows per thread stay in registers (N <= 4096); more go through the
+// snapshot, as in the passes, and take longer than those from N = 8000 on.
+// ---------------------------------------------------------------------------
+
+constexpr int kSmallThreads = 1024;
+static_assert(kSmallBuildN == 4 * kSmallThreads && kSmallBuildRareN == 16 * kSmallThreads, "rows per thread");
+
+template <int ROWS, bool HOLD>
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(CellArgs a)
+{
+    if (!gate_open(a.gate)) return;
+    constexpr int kMax = ROWS * kSmallThreads;
+    __shared__ int32_t start[kSmallBuildCells];   // counts, then the cells' first positions
+    __shared__ int32_t member[kMax];              // caller indices by cell, unordered
+    __shared__ int32_t wsum[kSmallThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    for (int c = t; c < a.g.ncell; c += kSmallThreads) start[c] = 0;
+    __syncthreads();
+    int id[ROWS], slot[ROWS];
+    CellRow row[HOLD ? ROWS : 1];
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+        const int p = k * kSmallThreads + t;
+        if (p < a.N) {
+            if constexpr (HOLD) {
+                row[k].x = a.xs[p];
+                row[k].order = a.order[p];
+                row[k].m = a.ms[p];
+                if (a.vs)
+                    for (int d = 0; d < 3; ++d) row[k].v[d] = a.vs[d * a.N + p];
+                id[k] = cell_of(a.g, row[k].x);
+            } else {
+                id[k] = cell_id_of(a, p);
+            }
+            slot[k] = atomicAdd(&start[id[k]], 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan: thread t takes cells [t per, (t + 1) per)
+    const int per = (a.g.ncell + kSmallThreads - 1) / kSmallThreads;
+    int n = 0;
+    for (int k = 0; k < per; ++k)
+        if (t * per + k < a.g.ncell) n += start[t * per + k];
+    int incl = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(incl, off);
+        if (lane >= off) incl += u;
+    }
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    int run = incl - n;
+    for (int w = 0; w < wv; ++w) run += wsum[w];
+    for (int k = 0; k < per; ++k) {
+        const int c = t * per + k;
+        if (c < a.g.ncell) {
+            const int cnt = start[c];
+            start[c] = run;
+            a.cell_start[c] = run;
+            run += cnt;
+        }
+    }
+    if (t == 0) a.cell_start[a.g.ncell] = a.N;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+        const int p = k * kSmallThreads + t;
+        if (p < a.N) member[start[id[k]] + slot[k]] = HOLD ? row[HOLD ? k : 0].order : a.order_old[p];
+    }
+    __syncthreads();   // every row has been read: the new order may overwrite them
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+        const int p = k * kSmallThreads + t;
+        if (p < a.N) {
+            const int cb = start[id[k]], ce = id[k] + 1 < a.g.ncell ? start[id[k] + 1] : a.N;
+            const int key = HOLD ? row[HOLD ? k : 0].order : a.order_old[p];
+            int r = 0;
+            for (int m = cb; m < ce; ++m) r += (member[m] < key);
+            if constexpr (HOLD) place_row(a, row[k], cb + r);
+            else place_row(a, old_row(a, p), cb + r);
+        }
+    }
+}
 
 static bool cell_args_ok(const CellArgs &a)
 {
@@ -223,6 +341,11 @@ static bool cell_args_ok(const CellArgs &a)
 hipError_t launch_cell_build(const CellArgs &a, hipStream_t st)
 {
     if (!cell_args_ok(a)) return hipErrorInvalidValue;
+    if (a.g.ncell <= kSmallBuildCells && a.N <= (a.rare ? kSmallBuildRareN : kSmallBuildN)) {
+        if (a.N <= kSmallBuildN) hipLaunchKernelGGL((k_build_small<4, true>), dim3(1), dim3(kSmallThreads), 0, st, a);
+        else hipLaunchKernelGGL((k_build_small<16, false>), dim3(1), dim3(kSmallThreads), 0, st, a);
+        return hipGetLastError();
+    }
     int grid = (a.N + kBlock - 1) / kBlock;
     int nt = scan_tiles(a.g.ncell);
     hipLaunchKernelGGL(k_cell_ids, dim3(grid), dim3(kBlock), 0, st, a);

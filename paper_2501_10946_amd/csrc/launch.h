@@ -97,8 +97,17 @@ struct CellArgs {
     int32_t *tile_sum;     // [scan_tiles(ncell)] scan workspace
     int32_t *ticket;       // scan's finished-tile counter: zero between builds
     const int32_t *gate;   // null: always build; else build only when *gate != 0
+    int rare;              // the gate is closed in most launches (lists with a skin)
 };
 __host__ __device__ inline int scan_tiles(int ncell) { return (ncell + kScanTile - 1) / kScanTile; }
+// Systems of at most kSmallBuildCells cells built by one workgroup in one launch:
+// up to kSmallBuildN particles always (rebuilt every step, us a step against the
+// five launches: N = 1000 36 and 51, 4000 44 and 53), up to kSmallBuildRareN
+// where the gate is mostly closed (N = 10 007, rebuilt every ~15 steps: 30 and
+// 37; rebuilt every step N = 8000 would take 75 us instead of 55).
+constexpr int kSmallBuildCells = 16384;
+constexpr int kSmallBuildN = 4096;
+constexpr int kSmallBuildRareN = 16384;
 // ids + counts + snapshot, scan (which leaves the counts zero again), scatter,
 // stable rank + move; `count` must be zero on entry
 hipError_t launch_cell_build(const CellArgs &a, hipStream_t st);
