@@ -102,6 +102,7 @@ Derived derive(const rbsog_params *p, const rbsog_sog *s)
     d.full_k = p->full_k ? 1 : 0;
     d.nmodes = d.full_k ? d.nlat : (int64_t)p->P;
     if (d.full_k) d.sbatch = 1;
+    d.erows = d.full_k ? 1 : kEnergyRows;
     return d;
 }
 
@@ -139,16 +140,18 @@ Layout make_layout(int64_t N, const Derived &d, int P, bool shared_lattice)
     L.ms = take(sizeof(double) * (size_t)N);
     L.ms_old = take(sizeof(double) * (size_t)N);
     const size_t nm = (size_t)d.nmodes;
+    // a replica of the ensemble adds its energies at every step
+    const size_t er = shared_lattice ? 1 : (size_t)d.erows;
     L.samp = take(sizeof(double) * 4 * (d.full_k ? nm : (size_t)P * (size_t)d.sbatch));
     L.part = take(d.full_k ? 0 : sizeof(double) * 2 * (size_t)nchunks(N, P) * (size_t)P);
     L.rho = take(sizeof(double) * 2 * nm);
     L.gk = take(sizeof(double) * 2 * nm);
-    L.eF = take(sizeof(double) * nm);
-    L.eW = take(sizeof(double) * nm);
+    L.eF = take(sizeof(double) * nm * er);
+    L.eW = take(sizeof(double) * nm * er);
     L.vm = take(sizeof(double) * ((size_t)d.mmax + 1));
     L.fnear = take(sizeof(double) * 3 * kNearLanes * (size_t)N);
-    L.epart = take(sizeof(double) * 2 * (size_t)near_blocks((int)N));
-    L.kepart = take(sizeof(double) * (size_t)far_blocks((int)N));
+    L.epart = take(sizeof(double) * 2 * (size_t)near_blocks((int)N) * er);
+    L.kepart = take(sizeof(double) * (size_t)far_blocks((int)N) * er);
     L.flag = take(sizeof(int32_t) * 8);
     L.energy = take(sizeof(double) * 8);
     L.nbr = take(sizeof(int32_t) * (size_t)list_rows(d.kp) * (size_t)list_padded(N));
@@ -157,7 +160,7 @@ Layout make_layout(int64_t N, const Derived &d, int P, bool shared_lattice)
     L.tab_far = take(sizeof(double) * 2 * kFarTable);
     L.cdf_q = take(sizeof(double) * (size_t)d.nshells);
     L.mh = take(sizeof(int32_t) * 2);
-    L.bath = take(sizeof(double) * kBathWords);
+    L.bath = take(sizeof(double) * (kBathWords + kEnergyRows));
     L.fab = take(sizeof(double) * 2 * kMaxGauss);
     L.total = off;
     return L;
@@ -434,9 +437,10 @@ FarArgs far_args(rbsog_handle *h, const double4 *samp, double *f, double *f_near
     return fa;
 }
 
-EnergyArgs energy_args(rbsog_handle *h, double *out, bool kick)
+EnergyArgs energy_args(rbsog_handle *h, double *out, int rows, bool kick)
 {
     EnergyArgs ea{};
+    ea.rows = rows;
     ea.nnear = near_blocks((int)h->p.N);
     ea.nfar = far_blocks((int)h->p.N);
     ea.P = (int)h->d.nmodes;
@@ -467,7 +471,8 @@ Thermo thermo(const rbsog_handle *h, double dt, uint64_t step)
     return t;
 }
 
-BathArgs bath_args(const rbsog_handle *h, double dt, int mode)
+// The bath's half-steps around the step whose partials went to set eset.
+BathArgs bath_args(const rbsog_handle *h, double dt, int mode, int eset)
 {
     BathArgs b{};
     b.kind = h->bath_kind;
@@ -477,16 +482,21 @@ BathArgs bath_args(const rbsog_handle *h, double dt, int mode)
     b.rate = h->bath_rate;
     b.Q = b.gkT / (h->bath_rate * h->bath_rate);
     b.nfar = far_blocks((int)h->p.N);
-    b.kepart = h->kepart;
+    b.kepart = h->kepart + (size_t)eset * b.nfar;
     b.bath = h->bath;
+    b.ke = h->bath + kBathWords + eset;
     return b;
 }
 
-int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bool kick, double dt, double *energy,
+int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bool kick, double dt, int eset,
              int32_t *gate_raise, int32_t *gate_clear, uint64_t next_step, int bath_mode)
 {
+    const size_t es = (size_t)std::max(eset, 0);
     RhoArgs ra = rho_args(h, samp);
-    NearArgs na = near_args(h, nullptr, energy != nullptr);
+    ra.eF += es * (size_t)ra.P;
+    ra.eW += es * (size_t)ra.P;
+    NearArgs na = near_args(h, nullptr, eset >= 0);
+    na.epart += es * 2 * (size_t)near_blocks((int)h->p.N);
     if (h->d.full_k) {
         HIPCHECK(timed(h, kRhoPartial, [&] { return launch_rho_full(ra, h->st); }));
     } else {
@@ -507,6 +517,7 @@ int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bo
     HIPCHECK(timed(h, kNear, [&] { return launch_near(na, h->st); }));
     if (!h->d.full_k) HIPCHECK(timed(h, kRhoReduce, [&] { return launch_rho_reduce(ra, h->st); }));
     FarArgs fa = far_args(h, samp, f, f_near, kick, dt);
+    if (fa.kepart) fa.kepart += es * (size_t)far_blocks((int)h->p.N);
     fa.gate_clear = gate_clear;
     fa.rebuilds = gate_clear ? h->rebuilds : nullptr;
     if (kick && gate_raise) {
@@ -522,12 +533,16 @@ int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bo
     HIPCHECK(timed(h, kFar, [&] { return launch_far(fa, h->st); }));
     // a global bath: the step's closing half-step (and the next one's opening)
     // on the kinetic energy the far kernel's half-kick left
-    if (kick && bath_mode) HIPCHECK(timed(h, kKickDrift, [&] { return launch_bath(bath_args(h, dt, bath_mode), h->st); }));
-    if (energy) {
-        EnergyArgs ea = energy_args(h, energy, kick);
-        if (kick && bath_mode) ea.ke_set = h->bath + 3;
-        HIPCHECK(timed(h, kEnergy, [&] { return launch_energy(ea, h->st); }));
-    }
+    if (kick && bath_mode)
+        HIPCHECK(timed(h, kKickDrift, [&] { return launch_bath(bath_args(h, dt, bath_mode, (int)es), h->st); }));
+    return RBSOG_OK;
+}
+
+int energy_rows(rbsog_handle *h, double *out, int rows, bool kick, bool bath)
+{
+    EnergyArgs ea = energy_args(h, out, rows, kick);
+    if (kick && bath) ea.ke_set = h->bath + kBathWords;
+    HIPCHECK(timed(h, kEnergy, [&] { return launch_energy(ea, h->st); }));
     return RBSOG_OK;
 }
 
@@ -883,7 +898,8 @@ extern "C" int rbsog_compute_forces(rbsog_handle *h, uint64_t step, const double
     const double4 *samp = nullptr;
     rc = modes(h, step, 1, &samp);
     if (rc) return rc;
-    return evaluate(h, samp, f_dev, f_near_dev, false, 0.0, energy_dev);
+    rc = evaluate(h, samp, f_dev, f_near_dev, false, 0.0, energy_dev ? 0 : -1);
+    return rc || !energy_dev ? rc : energy_rows(h, energy_dev, 1, false, false);
 }
 
 namespace rbsog {
@@ -977,7 +993,7 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
         k.order = h->order;
         if (global) {   // the first step's opening half-step of the bath
             HIPCHECK(timed(h, kKickDrift, [&] { return launch_ke_partials(k.N, h->vs, h->ms, h->kepart, h->st); }));
-            HIPCHECK(timed(h, kKickDrift, [&] { return launch_bath(bath_args(h, dt, 1), h->st); }));
+            HIPCHECK(timed(h, kKickDrift, [&] { return launch_bath(bath_args(h, dt, 1, 0), h->st); }));
             k.vscale = h->bath + 2;
         }
         HIPCHECK(timed(h, kKickDrift, [&] { return launch_kick_drift(k, h->st); }));
@@ -990,13 +1006,17 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
         uint64_t step = step0 + (uint64_t)n + 1;
         rc = modes(h, step, nsteps - n, &samp);
         if (rc) return rc;
-        double *e = energy_hist_dev ? energy_hist_dev + kEnergyCols * (size_t)n : nullptr;
+        const int eset = energy_hist_dev ? n % h->d.erows : -1;
         const bool last = n + 1 == nsteps;
         // a global bath keeps the next step's half-kick and drift out of the far
         // kernel: its velocity factor needs the whole system's kinetic energy
-        rc = evaluate(h, samp, nullptr, nullptr, true, dt, e, (last || global) ? nullptr : gate_next, gate, step + 1,
+        rc = evaluate(h, samp, nullptr, nullptr, true, dt, eset, (last || global) ? nullptr : gate_next, gate, step + 1,
                       global ? (last ? 2 : 3) : 0);
         if (rc) return rc;
+        if (eset >= 0 && (last || eset + 1 == h->d.erows)) {   // the rows of the sets filled since the last time
+            rc = energy_rows(h, energy_hist_dev + kEnergyCols * (size_t)(n - eset), eset + 1, true, global);
+            if (rc) return rc;
+        }
         if (global && !last) {
             KickDriftArgs k{};
             k.N = (int)h->p.N;

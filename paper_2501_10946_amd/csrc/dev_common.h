@@ -52,6 +52,23 @@ __device__ inline double block_sum_256(double v, double *red)
     return red[0];
 }
 
+// A thread's share of the sum of v[0 .. n) over a kBlock-thread workgroup (added
+// in index order), eight loads in flight.
+__device__ inline double strided_sum(const double *v, int n)
+{
+    double s = 0.0;
+    int b = threadIdx.x;
+    for (; b + 7 * kBlock < n; b += 8 * kBlock) {
+        double u[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) u[k] = v[b + k * kBlock];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += u[k];
+    }
+    for (; b < n; b += kBlock) s += v[b];
+    return s;
+}
+
 // The thermostat's three normal deviates of particle i (caller index) for the
 // drift into force index `step`: four uniforms ((w >> 11) + 1) 2^-53 in (0, 1]
 // from Philox4x64-10(counter (i, step, 1, 0), key (seed, replica)) -- word 2 =

@@ -297,7 +297,7 @@ int write_tables(rbsog_ens *s, int r, double dt)
     fa.gate_clear = h->gate;
     if ((e = put(s->t_far, r, fa, s->up)) != hipSuccess) return ens_fail_hip(e, "far table");
     // energies of step E - e_adm go to row E - e_adm
-    EnergyArgs ea = energy_args(h, R.ehist, true);
+    EnergyArgs ea = energy_args(h, R.ehist, 1, true);
     ea.row0 = (uint64_t)0 - R.e_adm;
     if ((e = put(s->t_energy, r, ea, s->up)) != hipSuccess) return ens_fail_hip(e, "energy table");
     return RBSOG_OK;

@@ -40,14 +40,12 @@ __device__ inline double half_step(const BathArgs &a, double &xi, double &eta, d
 __global__ __launch_bounds__(kBlock) void k_bath(BathArgs a)
 {
     __shared__ double red[kBlock];
-    double k = 0.0;
-    for (int b = threadIdx.x; b < a.nfar; b += kBlock) k += a.kepart[b];
-    k = block_sum_256(k, red);
+    const double k = block_sum_256(strided_sum(a.kepart, a.nfar), red);
     if (threadIdx.x == 0) {
         double xi = a.bath[0], eta = a.bath[1], K = k, s = 1.0;
         if (a.mode & 2) {
             s = s * half_step(a, xi, eta, K);
-            a.bath[3] = K;
+            *a.ke = K;
         }
         if (a.mode & 1) s = s * half_step(a, xi, eta, K);
         a.bath[0] = xi;
@@ -87,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_scale_v(int N, double *__restrict__ 
 hipError_t launch_bath(const BathArgs &a, hipStream_t st)
 {
     if ((a.kind != kBathNoseHoover && a.kind != kBathBerendsen) || a.mode < 1 || a.mode > 3 || a.nfar < 1 ||
-        !a.kepart || !a.bath || !(a.dt > 0.0) || !(a.gkT > 0.0) || !(a.rate > 0.0) ||
+        !a.kepart || !a.bath || ((a.mode & 2) && !a.ke) || !(a.dt > 0.0) || !(a.gkT > 0.0) || !(a.rate > 0.0) ||
         (a.kind == kBathNoseHoover && !(a.Q > 0.0)))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_bath, dim3(1), dim3(kBlock), 0, st, a);

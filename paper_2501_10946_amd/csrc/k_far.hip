@@ -245,21 +245,19 @@ hipError_t launch_far(const FarArgs &a, hipStream_t st)
 // energies: fixed-order sums of the block partials
 // ---------------------------------------------------------------------------
 
-// shift: rows of `out` to skip (the ensemble writes row shift + row0)
-__device__ inline void energy_body(const EnergyArgs &a, uint64_t shift)
+// One workgroup per row: a step leaves the partials of its row in a set of its
+// own, and one launch adds up to kEnergyRows rows: a workgroup alone takes 5 us
+// at N = 1000 and took 48 at N = 1e6 (bound by the latency of its loads, eight
+// of which are now in flight), sixteen of them take as long as one.  row: the
+// set, and the row of `out` after the first `shift` (the ensemble writes row
+// shift + row0).
+__device__ inline void energy_body(const EnergyArgs &a, int row, uint64_t shift)
 {
     __shared__ double red[kBlock];
-    double un = 0.0, ke = 0.0, uf = 0.0, wn = 0.0, wf = 0.0;
-    for (int b = threadIdx.x; b < a.nnear; b += kBlock) {
-        un += a.epart[b];
-        wn += a.epart[a.nnear + b];
-    }
-    for (int l = threadIdx.x; l < a.P; l += kBlock) {
-        uf += a.eF[l];
-        wf += a.eW[l];
-    }
-    if (a.kepart)
-        for (int b = threadIdx.x; b < a.nfar; b += kBlock) ke += a.kepart[b];
+    const double *epart = a.epart + (size_t)row * 2 * a.nnear;
+    double un = strided_sum(epart, a.nnear), wn = strided_sum(epart + a.nnear, a.nnear);
+    double uf = strided_sum(a.eF + (size_t)row * a.P, a.P), wf = strided_sum(a.eW + (size_t)row * a.P, a.P);
+    double ke = a.kepart ? strided_sum(a.kepart + (size_t)row * a.nfar, a.nfar) : 0.0;
     un = block_sum_256(un, red);
     __syncthreads();
     uf = block_sum_256(uf, red);
@@ -270,24 +268,27 @@ __device__ inline void energy_body(const EnergyArgs &a, uint64_t shift)
     __syncthreads();
     wf = block_sum_256(wf, red);
     if (threadIdx.x == 0) {
-        double *o = a.out + kEnergyCols * (shift + a.row0);
+        double *o = a.out + kEnergyCols * (shift + a.row0 + (uint64_t)row);
         o[0] = un;
         o[1] = uf;
         o[2] = a.Uk0;
         o[3] = a.Uself;
         o[4] = a.Ubg;
-        o[5] = a.ke_set ? *a.ke_set : ke;
+        o[5] = a.ke_set ? a.ke_set[row] : ke;
         o[6] = wn;
         o[7] = wf;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a) { energy_body(a, 0); }
+__global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a)
+{
+    energy_body(a, (int)blockIdx.x, 0);
+}
 
 __global__ __launch_bounds__(kBlock) void k_energy_batch(const EnergyArgs *__restrict__ tab,
                                                          const EnsItem *__restrict__ items, const uint64_t *shift)
 {
-    energy_body(tab[items[blockIdx.x].r], *shift);
+    energy_body(tab[items[blockIdx.x].r], 0, *shift);
 }
 
 hipError_t launch_energy_batch(const EnergyArgs *tab, const EnsItem *items, int n, const uint64_t *shift,
@@ -300,8 +301,8 @@ hipError_t launch_energy_batch(const EnergyArgs *tab, const EnsItem *items, int 
 
 hipError_t launch_energy(const EnergyArgs &a, hipStream_t st)
 {
-    if (!a.epart || !a.eF || !a.eW || !a.out) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_energy, dim3(1), dim3(kBlock), 0, st, a);
+    if (!a.epart || !a.eF || !a.eW || !a.out || a.rows < 1 || a.rows > kEnergyRows) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_energy, dim3(a.rows), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }
 

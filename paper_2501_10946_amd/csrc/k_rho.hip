@@ -67,6 +67,9 @@ int rho_chunk_shared(int N, int P, bool mixed)
     int c = 1;
     while (2 * c <= kRhoChunkMax && rho_lds_bytes(P, 2 * c, mixed, false) <= 16384 && (255 / P + 2) * 2 * c <= kRhoStage)
         c *= 2;
+    // (smaller groups for small systems, at least 512 to 4096 waves of them, were
+    // tried: N = 10 007 31 -> 32 to 37 us a step, the reduction's and the far
+    // kernel's wait for more partials costs more than the shorter chains save)
     return std::max(c, rho_chunk(N, P));
 }
 

@@ -363,16 +363,18 @@ hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, boo
 // --- energies ---------------------------------------------------------------
 // An energy row: U_N, U*_F, U_k0, U_self, U_bg, KE, W_N, W*_F.
 constexpr int kEnergyCols = 8;
+constexpr int kEnergyRows = 16;   // sets of partials a single system keeps: rows one launch adds
 struct EnergyArgs {
+    int rows;                  // 1 .. kEnergyRows (single system)
     int nnear, nfar, P;
-    const double *epart;       // [2][nnear]: energy, then virial partials
-    const double *kepart;      // [nfar] or null
-    const double *eF;          // [P]
-    const double *eW;          // [P]
+    const double *epart;       // [rows][2][nnear]: energy, then virial partials
+    const double *kepart;      // [rows][nfar] or null
+    const double *eF;          // [rows][P]
+    const double *eW;          // [rows][P]
     double Uk0, Uself, Ubg;
-    double *out;               // [rows][kEnergyCols]; one system writes row row0
+    double *out;               // rows of kEnergyCols; one system writes rows row0 ...
     uint64_t row0;
-    const double *ke_set;      // null, or the kinetic energy to report (a global bath's, after its half-step)
+    const double *ke_set;      // null, or [rows] kinetic energies to report (a global bath's, after its half-step)
 };
 hipError_t launch_energy(const EnergyArgs &a, hipStream_t st);
 // ensemble: one item per replica; each writes row *shift + row0 of its out
@@ -383,7 +385,7 @@ hipError_t launch_energy_batch(const EnergyArgs *tab, const EnsItem *items, int 
 // --- global baths (Nose-Hoover, Berendsen) ------------------------------------
 // The bath state lives on the device: kBathWords doubles, [0] xi, [1] eta (the
 // Nose-Hoover friction and its time integral), [2] the factor the velocities
-// take next, [3] the kinetic energy after the last closing half-step.
+// take next.
 constexpr int kBathWords = 8;
 constexpr int kBathNoseHoover = 2, kBathBerendsen = 3;
 struct BathArgs {
@@ -393,6 +395,7 @@ struct BathArgs {
     int nfar;
     const double *kepart;      // [nfar] kinetic-energy partials of the current velocities
     double *bath;              // [kBathWords]
+    double *ke;                // the kinetic energy after the closing half-step (modes 2 and 3)
 };
 hipError_t launch_bath(const BathArgs &a, hipStream_t st);
 // kinetic-energy partials of vs (cell order) in the far kernel's blocks

@@ -51,6 +51,7 @@ struct Derived {
     int sbatch;        // steps whose modes one sampling launch draws
     int full_k;        // deterministic far field over the whole lattice
     int64_t nmodes;    // modes of one evaluation: P, or nlat with full_k
+    int erows;         // sets of energy partials a run of steps fills before they are added
 };
 
 size_t align_up(size_t v);
@@ -168,7 +169,7 @@ RhoArgs rho_args(rbsog_handle *h, const double4 *samp);
 // f, f_near: caller-order outputs (may be null); kick: write the cell-order
 // forces and apply the second half-kick to the cell-order velocities
 FarArgs far_args(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bool kick, double dt);
-EnergyArgs energy_args(rbsog_handle *h, double *out, bool kick);
+EnergyArgs energy_args(rbsog_handle *h, double *out, int rows, bool kick);
 // cell order + lists of the fine grid from the rows in xs (gated or not)
 int prepare(rbsog_handle *h, const int32_t *gate, bool carry_v);
 // The default skin against the time step dt: when the fastest thermal velocity
@@ -193,9 +194,12 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
 // step's first half-kick and drift, raising gate_raise; gate_clear is cleared
 // the thermostat of a step's drift into force index `step` (off without friction)
 Thermo thermo(const rbsog_handle *h, double dt, uint64_t step);
-// with gate_raise the far kernel also drifts into force index next_step
-int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bool kick, double dt, double *energy,
+// with gate_raise the far kernel also drifts into force index next_step;
+// eset >= 0: leave the energy partials in set eset
+int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bool kick, double dt, int eset,
              int32_t *gate_raise = nullptr, int32_t *gate_clear = nullptr, uint64_t next_step = 0,
              int bath_mode = 0);
+// the energy rows of the sets 0 .. rows - 1 into out; kick, bath: as evaluated
+int energy_rows(rbsog_handle *h, double *out, int rows, bool kick, bool bath);
 
 }  // namespace rbsog
