@@ -50,6 +50,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dev_common.h"
+#include "dev_window.h"
 
 namespace rbsog {
 
@@ -74,7 +75,6 @@ __device__ inline NearMem &near_args_again(NearMem &a)
     return *p;
 }
 
-__device__ inline double shift_of(int code, double L) { return (double)(code - 1) * L; }
 
 // Distance from coordinate y to the slab [c w - m, (c + 1) w + m] (0 inside).
 __device__ inline double slab_gap(double y, int c, double w, double m)
@@ -348,107 +348,6 @@ __device__ inline double readlane_f64(double v, int l)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// The window of cell pair q: two x-adjacent cells of the fine grid (the last
-// cell of a row of odd length alone) hold the home particles [h_beg, h_end);
-// their candidates are the particles of 25 rows (dz, dy = -2..2) of the cells
-// x0 - 2 .. x1 + 2, each row one contiguous range of the cell order or two
-// where it wraps, 50 pieces at most.  Lane l < 50 describes piece l in the wave's
-// tables.
-// Returns false, uniformly over the wave, when q is past the last pair or the
-// pair has no home particle.  A window holds each particle at most once: it is
-// at most 6 cells wide in x and 5 in y and z, and the grid has at least 6.
-// Positions are taken relative to the pair's centre, so that a distance test
-// can be written out as |c|^2 - 2 h.c + |h|^2 without losing its digits.
-struct PairWindow {
-    int h_beg, h_end, total;   // home particles; candidates (all uniform)
-};
-
-struct PairTables {            // one wave's window, by piece
-    int32_t pref[64];          // exclusive prefix sums of the pieces' lengths
-    int32_t first[64];         // particle index of candidate c of the piece, less c
-    double shift[3][64];       // image shift less the centre
-};
-
-__device__ inline bool pair_window(const NearArgs &a, int q, PairTables &w, double centre[3], PairWindow &win)
-{
-    const int lane = threadIdx.x & 63;
-    const int nf = a.g.nc[0], nfy = a.g.nc[1], nfz = a.g.nc[2], half = (nf + 1) >> 1;
-    if (q >= nfz * nfy * half) return false;
-    const int row = q / half, ix = q - row * half;
-    const int cz = row / nfy, cy = row - cz * nfy;
-    const int x0 = 2 * ix, x1 = min(x0 + 1, nf - 1);
-    const int cbase = (cz * nfy + cy) * nf;
-    win.h_beg = __builtin_amdgcn_readfirstlane(a.cell_start[cbase + x0]);
-    win.h_end = __builtin_amdgcn_readfirstlane(a.cell_start[cbase + x1 + 1]);
-    if (win.h_beg >= win.h_end) return false;
-    centre[0] = (double)(x0 + 1) * a.w[0];
-    centre[1] = ((double)cy + 0.5) * a.w[1];
-    centre[2] = ((double)cz + 0.5) * a.w[2];
-    int ps = 0, plen = 0, xc = 1, yc = 1, zc = 1;
-    if (lane < 2 * 25) {
-        const int r = lane >> 1, k = lane & 1;
-        int czw = cz + r / 5 - 2;
-        if (czw < 0) { czw += nfz; zc = 0; } else if (czw >= nfz) { czw -= nfz; zc = 2; }
-        int cyw = cy + r % 5 - 2;
-        if (cyw < 0) { cyw += nfy; yc = 0; } else if (cyw >= nfy) { cyw -= nfy; yc = 2; }
-        const int rb = (czw * nfy + cyw) * nf;
-        const int xa = x0 - 2, xb = x1 + 2;   // at most 6 cells <= nf: one side wraps at most
-        int lo = xa, hi = xb;
-        bool has = k == 0;
-        if (xa < 0) {
-            has = true;
-            if (k == 0) { lo = xa + nf; hi = nf - 1; xc = 0; } else { lo = 0; hi = xb; }
-        } else if (xb > nf - 1) {
-            has = true;
-            if (k == 0) { hi = nf - 1; } else { lo = 0; hi = xb - nf; xc = 2; }
-        }
-        if (has) {
-            ps = a.cell_start[rb + lo];
-            plen = a.cell_start[rb + hi + 1] - ps;
-        }
-    }
-    int incl = plen;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int u = __shfl_up(incl, off);
-        if (lane >= off) incl += u;
-    }
-    win.total = __builtin_amdgcn_readlane(incl, 63);
-    w.pref[lane] = incl - plen;
-    w.first[lane] = ps - (incl - plen);
-    w.shift[0][lane] = shift_of(xc, a.g.L[0]) - centre[0];
-    w.shift[1][lane] = shift_of(yc, a.g.L[1]) - centre[1];
-    w.shift[2][lane] = shift_of(zc, a.g.L[2]) - centre[2];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    return true;
-}
-
-// The piece of cell pair q's window that holds its home particles (see
-// pair_window): the central row's first piece, or its second when the row
-// wraps at the low x side.
-__device__ inline int pair_window_home_piece(const NearArgs &a, int q)
-{
-    const int half = (a.g.nc[0] + 1) >> 1;
-    const int ix = q - (q / half) * half;
-    return 2 * ix - 2 < 0 ? 25 : 24;
-}
-
-// The piece of candidate c (< the window's total): the last piece whose prefix
-// is <= c (an empty piece shares the prefix of the next, so it is never the
-// one found), by binary search over the 64 prefixes.
-__device__ inline int window_piece(const int32_t *ppref, int c)
-{
-    int lo = 0, n = 64;
-    while (n > 0) {
-        int h2 = n >> 1;
-        if (ppref[lo + h2] <= c) { lo += h2 + 1; n -= h2 + 1; }
-        else n = h2;
-    }
-    return lo - 1;
-}
-
 // One wave lists the neighbours of the home particles of cell pair q,
 // kListHomes of them per pass over the window.  Lanes take 64 consecutive
 // candidates of the window at a time (loads coalesced along the rows); each
@@ -470,11 +369,6 @@ __device__ inline int window_piece(const int32_t *ppref, int c)
 // scalar instructions a test, the launch took 0.54 ms).  N = 1e6 plasma: 0.44
 // -> 0.37 ms a build, 222 -> 169 M vector instructions.
 constexpr int kListHomes = 16;
-// windows of up to this many candidates get a table of each candidate's piece
-// (one byte each, in LDS), written once per window: a lookup per candidate in
-// place of a binary search per chunk of candidates, which the few home
-// particles of a cell pair (~8 at the N = 1e6 plasma) would otherwise share
-constexpr int kPieceTab = 2048;
 static_assert(kListBlock == 8, "a list block is read as two int4");
 
 // The tests of homes hp and hp + 1 of a pass against a chunk of 64 candidates
@@ -514,23 +408,16 @@ __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
     PairTables &w = tabs[wv];
     PairWindow win;
     double centre[3];
-    if (!pair_window(a, q, w, centre, win)) return;   // uniform per wave
+    if (!pair_window<true>(a.g, a.w, a.cell_start, q, w, centre, win)) return;   // uniform per wave
     const int total = win.total;
-    const bool tabled = total <= kPieceTab;   // uniform
-    if (tabled) {   // lane l writes its piece's index over the piece's candidates
-        const int b0 = w.pref[lane], b1 = lane < 63 ? w.pref[lane + 1] : total;
-        for (int t = b0; t < b1; ++t) pidx[wv][t] = (uint8_t)lane;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
+    const bool tabled = window_pieces(w, total, pidx[wv]);   // uniform
     const uint32_t rows = (uint32_t)list_rows(a.kp);
     // The home particles are consecutive candidates of the window's central
     // row (dy = dz = 0, no image shift): piece 24 of that row, or piece 25
     // when the row wraps at the low x side (its first piece is then the
     // wrapped cells).  home_c is the candidate index of h_beg, so the lane
     // that holds a home itself follows from the lane's candidate index.
-    const int home_c = win.h_beg - __builtin_amdgcn_readfirstlane(w.first[pair_window_home_piece(a, q)]);
+    const int home_c = win.h_beg - __builtin_amdgcn_readfirstlane(w.first[pair_window_home_piece(a.g, q)]);
     // the list radius squared with a relative margin of 1e-12 and the rounding
     // of an image-shifted position (a few ulp of the box edge): a candidate is
     // tested in another form than the evaluation's difference, and a pair on
@@ -549,9 +436,7 @@ __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
             }
             home[wv][lane] = h;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
         // the pass's homes' lists are consecutive rows from pass_row on; slot[hh]
         // is the next entry of home hh counted from pass_row (hh rows + count;
         // a wave-uniform value held in a vector register, where mbcnt adds it)
@@ -590,9 +475,7 @@ __device__ inline void nlist_pair(const NearArgs &a, int q, int wv)
             if (mine == 0) pass_row[(uint32_t)lane * rows] = hb + lane;   // entry 0 is always a valid index
         }
         // the positions of the next pass overwrite these
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     }
 }
 
