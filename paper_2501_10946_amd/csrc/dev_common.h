@@ -326,8 +326,10 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
         }
         double cf = a.samp[l].w;
         a.rho[l] = make_double2(re, im);
-        a.gk[l] = far_coef(a.mixed, cf, re, im);
-        a.eF[l] = 0.5 * cf * (re * re + im * im);
+        if (a.gk) {   // a step's modes: the far field's coefficients and the energies
+            a.gk[l] = far_coef(a.mixed, cf, re, im);
+            a.eF[l] = 0.5 * cf * (re * re + im * im);
+        }
         if (a.eW) a.eW[l] = cf * (re * re + im * im) * (1.5 - mode_vm(a, a.samp[l]));
         if (a.rho_out) {
             a.rho_out[2 * l] = re;

@@ -91,7 +91,7 @@ hipError_t launch_rho_partial(const RhoArgs &a, hipStream_t st)
 
 hipError_t launch_rho_reduce(const RhoArgs &a, hipStream_t st)
 {
-    if (!a.part || !a.rho || !a.gk || !a.eF || !a.samp || (a.eW && !vm_ok(a))) return hipErrorInvalidValue;
+    if (!a.part || !a.rho || !a.gk != !a.eF || !a.samp || (a.eW && !vm_ok(a))) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_rho_reduce, dim3(rho_reduce_blocks(a.P)), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }

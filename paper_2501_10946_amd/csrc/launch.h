@@ -204,7 +204,7 @@ struct RhoArgs {
     const double4 *samp;       // [P]
     double2 *part;             // [nchunk][P] partial sums per (group, sample)
     double2 *rho;              // [P]
-    double2 *gk;               // [P] far-field coefficients (far_coef)
+    double2 *gk;               // [P] far-field coefficients (far_coef); null (with eF): the sums alone
     double *eF;                // [P] coef |rho|^2 / 2
     double *eW;                // null, or [P] coef |rho|^2 (3/2 - vm): the modes' far-field virial terms
     const double *vm;          // [m_max + 1] vm = k^2 G / Fhat by |n|^2 (a cube, when eW)
