@@ -129,6 +129,33 @@ __device__ inline double kick_drift_row(double x[3], double v[3], const double f
     return d2;
 }
 
+// First half-kick and drift of workgroup b's rows; raises the rebuild gate of
+// this step and clears the next one's (when the caller alternates two).
+__device__ inline void kick_drift_body(const KickDriftArgs &a, int b)
+{
+    int p = b * kBlock + threadIdx.x;
+    if (p == 0 && a.gate_next) *a.gate_next = 0;
+    if (p >= a.N) return;
+    const double hm = (0.5 * a.dt) / a.ms[p];
+    const double4 r = a.xs[p];
+    double x[3] = {r.x, r.y, r.z};
+    double v[3] = {a.vs[p], a.vs[a.N + p], a.vs[2 * a.N + p]};
+    if (a.vscale) {   // a global bath's half-steps since the last kick
+        const double sc = *a.vscale;
+        v[0] = v[0] * sc;
+        v[1] = v[1] * sc;
+        v[2] = v[2] * sc;
+    }
+    const double f[3] = {a.fs[p], a.fs[a.N + p], a.fs[2 * a.N + p]};
+    bool bad = false;
+    double d2 = kick_drift_row(x, v, f, hm, a.dt, a.L, a.inv_L, a.xb, a.N, p, &bad, a.th,
+                               a.th.on ? (uint64_t)a.order[p] : 0, a.ms[p]);
+    for (int d = 0; d < 3; ++d) a.vs[d * a.N + p] = v[d];
+    a.xs[p] = make_double4(x[0], x[1], x[2], r.w);
+    raise_any(a.flag, bad);
+    raise_gate(a.gate, d2, a.half_skin2, p);
+}
+
 // ---------------------------------------------------------------------------
 // structure factors.  Particles are cut into groups of C (the "chunk") and the
 // lanes of the grid are laid out flat over (group s, sample l), lane s P + l,

@@ -89,14 +89,14 @@ struct Replica {
     size_t off = 0, bytes = 0;
     double *x = nullptr, *v = nullptr, *f = nullptr, *q = nullptr, *m = nullptr, *ehist = nullptr;
     int64_t N = 0;
-    int P = 0, ng = 0, nsteps = 0;
+    int P = 0, nsteps = 0;
     bool mixed = false;
+    NearKind kind = NearKind::kMixed;
     uint64_t e_adm = 0;   // ensemble steps launched before the replica's first
     uint64_t e_done = 0;  // ensemble step count after its last step
 };
 
 constexpr int kEnsEvents = 8192;  // completion events kept (ring)
-constexpr int kGroups = 10;       // near-field groups: Gaussian count (0: run-time count), 9: polynomial sums
 
 // A device array grown on demand (the ensemble's own bookkeeping, outside the pool).
 template <class T>
@@ -145,8 +145,7 @@ struct rbsog_ens {
     EnergyArgs *t_energy = nullptr;
     // work lists: one device buffer, offsets and counts per list
     DevVec<EnsItem> items;
-    enum { L256, LTILE, LNLIST, LSAMP, LENERGY, LRHO0, LRHO1, LRED0, LRED1, LFAR0, LFAR1, LNEAR0, LNEAR1 = LNEAR0 + kGroups,
-           NLISTS = LNEAR1 + kGroups };
+    enum { LKICK, L256, LTILE, LNLIST, LENERGY, LRED, LFAR0, LFAR1, LNEARMIXED, LNEARPOLY, LNEAREXP, NLISTS };
     size_t off[NLISTS] = {};
     int cnt[NLISTS] = {};
     size_t rho_lds[2] = {};
@@ -174,10 +173,10 @@ namespace {
 
 int ens_fail_hip(hipError_t e, const char *what) { return fail(RBSOG_EHIP, "%s: %s", what, hipGetErrorString(e)); }
 
-// The last node of a step: the device's ensemble step counter moves on.
-__global__ void k_ens_advance(uint64_t *E)
+int near_list_of(NearKind k)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) E[0] = E[0] + 1;
+    return k == NearKind::kMixed ? rbsog_ens::LNEARMIXED : k == NearKind::kPoly ? rbsog_ens::LNEARPOLY
+                                                                                : rbsog_ens::LNEAREXP;
 }
 
 void drop_graph(rbsog_ens *s)
@@ -197,6 +196,7 @@ int rebuild_lists(rbsog_ens *s)
         if (s->rep[r].active) order.push_back(r);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return s->rep[a].N > s->rep[b].N; });
     std::vector<std::vector<EnsItem>> L(rbsog_ens::NLISTS);
+    std::vector<EnsItem> rho[2];   // structure-factor partials by precision
     size_t lds[2] = {0, 0};
     for (int r : order) {
         const Replica &R = s->rep[r];
@@ -208,14 +208,36 @@ int rebuild_lists(rbsog_ens *s)
         add(rbsog_ens::L256, (N + kBlock - 1) / kBlock);
         add(rbsog_ens::LTILE, scan_tiles(h->gf.ncell));
         add(rbsog_ens::LNLIST, nlist_blocks(h->gf.nc));
-        add(rbsog_ens::LSAMP, (R.P + 63) / 64);
+        for (int b = 0; b < (R.P + kBlock - 1) / kBlock; ++b) L[rbsog_ens::LKICK].push_back(EnsItem{r, ~b});
         add(rbsog_ens::LENERGY, 1);
         const int chunk = rho_chunk_shared(N, R.P, R.mixed), nch = (N + chunk - 1) / chunk;   // as rho_args
-        add(rbsog_ens::LRHO0 + pr, rho_blocks(nch, R.P));
-        add(rbsog_ens::LRED0 + pr, rho_reduce_blocks(R.P));
+        for (int64_t b = 0; b < rho_blocks(nch, R.P); ++b) rho[pr].push_back(EnsItem{r, (int32_t)~b});
+        add(rbsog_ens::LRED, rho_reduce_blocks(R.P));
         add(rbsog_ens::LFAR0 + pr, far_blocks(N));
-        add((pr ? rbsog_ens::LNEAR1 : rbsog_ens::LNEAR0) + R.ng, near_blocks(N));
+        add(near_list_of(R.kind), near_blocks(N));
         lds[pr] = std::max(lds[pr], rho_lds_bytes(R.P, chunk, pr == 1, true));
+    }
+    // the draws run beside the drift
+    L[rbsog_ens::LKICK].insert(L[rbsog_ens::LKICK].end(), L[rbsog_ens::L256].begin(), L[rbsog_ens::L256].end());
+    // the partial sums run beside the near field of their precision, as in a
+    // system's own launch: before it when the chip holds them all at once, else
+    // spread evenly through it
+    for (int pr = 0; pr < 2; ++pr) {
+        std::vector<EnsItem> &near = L[pr ? rbsog_ens::LNEARMIXED
+                                          : L[rbsog_ens::LNEARPOLY].empty() ? rbsog_ens::LNEAREXP : rbsog_ens::LNEARPOLY];
+        const size_t nr = rho[pr].size(), nn = near.size();
+        std::vector<EnsItem> both;
+        both.reserve(nr + nn);
+        if ((int64_t)(nr + nn) < kInterleaveBlocks) {
+            both = rho[pr];
+            both.insert(both.end(), near.begin(), near.end());
+        } else {
+            for (size_t k = 0, at = 0; k < nn || at < nr;) {
+                while (at < nr && at * nn <= k * nr) both.push_back(rho[pr][at++]);
+                if (k < nn) both.push_back(near[k++]);
+            }
+        }
+        near.swap(both);
     }
     size_t total = 0;
     for (int k = 0; k < rbsog_ens::NLISTS; ++k) {
@@ -450,7 +472,6 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
     R.ehist = take(sizeof(double) * kEnergyCols * (size_t)nsteps);
     R.N = p->N;
     R.P = p->P;
-    R.ng = sog->n <= 8 ? sog->n : 0;
     R.mixed = p->precision == RBSOG_MIXED;
     R.nsteps = nsteps;
     // the state and the system's tables go up on the upload stream, which is
@@ -492,7 +513,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
         }
     }
     R.h->samp_n = 0;
-    if (!R.mixed && R.h->sd.poly) R.ng = 9;
+    R.kind = R.mixed ? NearKind::kMixed : R.h->sd.poly ? NearKind::kPoly : NearKind::kExp;
     R.e_adm = s->E;
     rc = write_tables(s, slot, dt);
     if (rc) {
@@ -513,31 +534,26 @@ hipError_t enqueue_step(rbsog_ens *s, hipStream_t st)
 {
     const EnsItem *it = s->items.p;
     auto list = [&](int k) { return it + s->off[k]; };
-    hipError_t e = launch_kick_drift_batch(s->t_kick, list(rbsog_ens::L256), s->cnt[rbsog_ens::L256], st);
+    hipError_t e = launch_kick_sample_batch(s->t_kick, s->t_samp, list(rbsog_ens::LKICK), s->cnt[rbsog_ens::LKICK],
+                                            s->E_dev, st);
     if (e == hipSuccess)
         e = launch_cell_build_batch(s->t_cell, list(rbsog_ens::L256), s->cnt[rbsog_ens::L256], list(rbsog_ens::LTILE),
                                     s->cnt[rbsog_ens::LTILE], st);
     if (e == hipSuccess) e = launch_nlist_batch(s->t_nlist, list(rbsog_ens::LNLIST), s->cnt[rbsog_ens::LNLIST], st);
-    if (e == hipSuccess)
-        e = launch_sample_batch(s->t_samp, list(rbsog_ens::LSAMP), s->cnt[rbsog_ens::LSAMP], s->E_dev, st);
-    for (int pr = 0; pr < 2 && e == hipSuccess; ++pr)
-        if (s->cnt[rbsog_ens::LRHO0 + pr] > 0)
-            e = launch_rho_batch(s->t_rho, list(rbsog_ens::LRHO0 + pr), s->cnt[rbsog_ens::LRHO0 + pr], s->rho_lds[pr],
-                                 pr == 1, list(rbsog_ens::LRED0 + pr), s->cnt[rbsog_ens::LRED0 + pr], st);
-    for (int pr = 0; pr < 2 && e == hipSuccess; ++pr)
-        for (int g = 0; g < kGroups && e == hipSuccess; ++g) {
-            int k = (pr ? rbsog_ens::LNEAR1 : rbsog_ens::LNEAR0) + g;
-            if (s->cnt[k] > 0) e = launch_near_batch(s->t_near, list(k), s->cnt[k], g, pr == 1, true, st);
-        }
-    for (int pr = 0; pr < 2 && e == hipSuccess; ++pr)
+    for (NearKind k : {NearKind::kPoly, NearKind::kExp, NearKind::kMixed}) {
+        const int l = near_list_of(k);
+        if (e == hipSuccess && s->cnt[l] > 0)
+            e = launch_near_batch(s->t_near, s->t_rho, list(l), s->cnt[l], k, s->rho_lds[k == NearKind::kMixed], st);
+    }
+    if (e == hipSuccess) e = launch_rho_reduce_batch(s->t_rho, list(rbsog_ens::LRED), s->cnt[rbsog_ens::LRED], st);
+    for (int pr = 0; pr < 2 && e == hipSuccess; ++pr) {
+        const bool last = pr == 1 || s->cnt[rbsog_ens::LFAR1] == 0;   // the step's last far field moves the counter on
         if (s->cnt[rbsog_ens::LFAR0 + pr] > 0)
-            e = launch_far_batch(s->t_far, list(rbsog_ens::LFAR0 + pr), s->cnt[rbsog_ens::LFAR0 + pr], pr == 1, st);
+            e = launch_far_batch(s->t_far, list(rbsog_ens::LFAR0 + pr), s->cnt[rbsog_ens::LFAR0 + pr], pr == 1,
+                                 last ? s->E_dev : nullptr, st);
+    }
     if (e == hipSuccess)
         e = launch_energy_batch(s->t_energy, list(rbsog_ens::LENERGY), s->cnt[rbsog_ens::LENERGY], s->E_dev, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_ens_advance, dim3(1), dim3(64), 0, st, s->E_dev);
-        e = hipGetLastError();
-    }
     return e;
 }
 

@@ -375,45 +375,14 @@ hipError_t launch_cell_build_batch(const CellArgs *tab, const EnsItem *per256, i
 // gates)
 // ---------------------------------------------------------------------------
 
-__device__ inline void kick_drift_body(const KickDriftArgs &a, int b)
-{
-    int p = b * kBlock + threadIdx.x;
-    if (p == 0 && a.gate_next) *a.gate_next = 0;
-    if (p >= a.N) return;
-    const double hm = (0.5 * a.dt) / a.ms[p];
-    const double4 r = a.xs[p];
-    double x[3] = {r.x, r.y, r.z};
-    double v[3] = {a.vs[p], a.vs[a.N + p], a.vs[2 * a.N + p]};
-    if (a.vscale) {   // a global bath's half-steps since the last kick
-        const double sc = *a.vscale;
-        v[0] = v[0] * sc;
-        v[1] = v[1] * sc;
-        v[2] = v[2] * sc;
-    }
-    const double f[3] = {a.fs[p], a.fs[a.N + p], a.fs[2 * a.N + p]};
-    bool bad = false;
-    double d2 = kick_drift_row(x, v, f, hm, a.dt, a.L, a.inv_L, a.xb, a.N, p, &bad, a.th,
-                               a.th.on ? (uint64_t)a.order[p] : 0, a.ms[p]);
-    for (int d = 0; d < 3; ++d) a.vs[d * a.N + p] = v[d];
-    a.xs[p] = make_double4(x[0], x[1], x[2], r.w);
-    raise_any(a.flag, bad);
-    raise_gate(a.gate, d2, a.half_skin2, p);
-}
-
-RBSOG_KERNELS(kick_drift, KickDriftArgs, kBlock)
+// (kick_drift_body is in dev_common.h: the ensemble draws its modes beside it)
+__global__ __launch_bounds__(kBlock) void k_kick_drift(KickDriftArgs a) { kick_drift_body(a, (int)blockIdx.x); }
 
 hipError_t launch_kick_drift(const KickDriftArgs &a, hipStream_t st)
 {
     if (a.N < 1 || !a.xs || !a.vs || !a.fs || !a.ms || !a.xb || !a.gate || !a.flag || (a.th.on && !a.order))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_kick_drift, dim3((a.N + kBlock - 1) / kBlock), dim3(kBlock), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_kick_drift_batch(const KickDriftArgs *tab, const EnsItem *per256, int n, hipStream_t st)
-{
-    if (!tab || !per256 || n < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_kick_drift_batch, dim3(n), dim3(kBlock), 0, st, tab, per256);
     return hipGetLastError();
 }
 

@@ -204,17 +204,19 @@ __global__ __launch_bounds__(kFarThreads) void k_far(FarArgs a)
 
 template <bool MIXED>
 __global__ __launch_bounds__(kFarThreads) void k_far_batch(const FarArgs *__restrict__ tab,
-                                                           const EnsItem *__restrict__ items)
+                                                           const EnsItem *__restrict__ items, uint64_t *advance)
 {
     const EnsItem e = items[blockIdx.x];
+    if (advance && blockIdx.x == 0 && threadIdx.x == 0) *advance += 1;
     far_body<MIXED, false, 1>(tab[e.r], e.b);
 }
 
-hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, hipStream_t st)
+hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, uint64_t *advance,
+                            hipStream_t st)
 {
     if (!tab || !items || n < 1) return hipErrorInvalidValue;
-    if (mixed) hipLaunchKernelGGL(k_far_batch<true>, dim3(n), dim3(kFarThreads), 0, st, tab, items);
-    else hipLaunchKernelGGL(k_far_batch<false>, dim3(n), dim3(kFarThreads), 0, st, tab, items);
+    if (mixed) hipLaunchKernelGGL(k_far_batch<true>, dim3(n), dim3(kFarThreads), 0, st, tab, items, advance);
+    else hipLaunchKernelGGL(k_far_batch<false>, dim3(n), dim3(kFarThreads), 0, st, tab, items, advance);
     return hipGetLastError();
 }
 
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a)
 __global__ __launch_bounds__(kBlock) void k_energy_batch(const EnergyArgs *__restrict__ tab,
                                                          const EnsItem *__restrict__ items, const uint64_t *shift)
 {
-    energy_body(tab[items[blockIdx.x].r], 0, *shift);
+    energy_body(tab[items[blockIdx.x].r], 0, *shift - 1);   // the far field has moved the counter on
 }
 
 hipError_t launch_energy_batch(const EnergyArgs *tab, const EnsItem *items, int n, const uint64_t *shift,

@@ -13,20 +13,12 @@ namespace rbsog {
 static bool vm_ok(const RhoArgs &a) { return a.vm || (a.nG >= 1 && a.nG <= kMaxGauss && a.fa && a.fb); }
 
 // Partial sums per (group, sample): rho_partial_body (shared with the near
-// kernel, which can run it in its first workgroups) is in dev_common.h.
+// kernels, which run it in some of their workgroups) is in dev_common.h.
 
 template <bool CELL, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_rho_partial(RhoArgs a)
 {
     rho_partial_body<CELL, MIXED, false>(a, (int)blockIdx.x);
-}
-
-template <bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_rho_partial_batch(const RhoArgs *__restrict__ tab,
-                                                              const EnsItem *__restrict__ items)
-{
-    const EnsItem e = items[blockIdx.x];
-    rho_partial_body<true, MIXED, true>(tab[e.r], e.b);   // the finer table, as the single system's step
 }
 
 // rho_reduce_body is in dev_common.h.
@@ -159,21 +151,15 @@ hipError_t launch_rho_full(const RhoArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-// Ensemble: one launch over every replica's groups (items: rho_blocks per
-// replica) with the largest staging any of them needs, then the reduction
-// (items: P per replica).
 size_t rho_lds_bytes(int P, int chunk, bool mixed, bool fine)
 {
     return sizeof(double4) * ((mixed ? 0 : (fine ? kFarTab : kPhaseTab) / 2) + (size_t)(255 / P + 2) * chunk);
 }
 
-hipError_t launch_rho_batch(const RhoArgs *tab, const EnsItem *part_items, int npart, size_t lds, bool mixed,
-                            const EnsItem *red_items, int nred, hipStream_t st)
+hipError_t launch_rho_reduce_batch(const RhoArgs *tab, const EnsItem *items, int n, hipStream_t st)
 {
-    if (!tab || !part_items || !red_items || npart < 1 || nred < 1 || lds > 65536) return hipErrorInvalidValue;
-    if (mixed) hipLaunchKernelGGL((k_rho_partial_batch<true>), dim3(npart), dim3(kBlock), lds, st, tab, part_items);
-    else hipLaunchKernelGGL((k_rho_partial_batch<false>), dim3(npart), dim3(kBlock), lds, st, tab, part_items);
-    hipLaunchKernelGGL(k_rho_reduce_batch, dim3(nred), dim3(kBlock), 0, st, tab, red_items);
+    if (!tab || !items || n < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_rho_reduce_batch, dim3(n), dim3(kBlock), 0, st, tab, items);
     return hipGetLastError();
 }
 

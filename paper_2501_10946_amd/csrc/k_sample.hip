@@ -14,9 +14,8 @@ namespace rbsog {
 constexpr int kSampleThreads = 64;
 
 // Draw idx of the launch: mode l of step a.step + shift + s, idx = s P + l.
-__device__ inline void sample_body(const SampleArgs &a, int b, uint64_t shift)
+__device__ inline void sample_body(const SampleArgs &a, int64_t idx, uint64_t shift)
 {
-    int64_t idx = (int64_t)b * kSampleThreads + threadIdx.x;
     if (idx >= (int64_t)a.P * a.nstep) return;
     int s = (int)(idx / a.P), l = (int)(idx - (int64_t)s * a.P);
     uint64_t w[4];
@@ -42,24 +41,31 @@ __device__ inline void sample_body(const SampleArgs &a, int b, uint64_t shift)
     if (a.coef_out) a.coef_out[l] = cf;
 }
 
-__global__ __launch_bounds__(kSampleThreads) void k_sample(SampleArgs a) { sample_body(a, (int)blockIdx.x, 0); }
-
-// Ensemble: one step per replica, the replica's step being its table entry's
-// step plus the ensemble step counter (read from device memory, so that a
-// captured launch sequence can be replayed step after step).
-__global__ __launch_bounds__(kSampleThreads) void k_sample_batch(const SampleArgs *__restrict__ tab,
-                                                                 const EnsItem *__restrict__ items,
-                                                                 const uint64_t *shift)
+__global__ __launch_bounds__(kSampleThreads) void k_sample(SampleArgs a)
 {
-    const EnsItem e = items[blockIdx.x];
-    sample_body(tab[e.r], e.b, *shift);
+    sample_body(a, (int64_t)blockIdx.x * kSampleThreads + threadIdx.x, 0);
 }
 
-hipError_t launch_sample_batch(const SampleArgs *tab, const EnsItem *items, int n, const uint64_t *shift,
-                               hipStream_t st)
+// Ensemble: the half-kick and drift of every replica and, in other workgroups of
+// the launch (items with b < 0), the draws of one step each, the replica's step
+// being its table entry's step plus the ensemble step counter (read from device
+// memory, so that a captured launch sequence can be replayed step after step).
+// The draws are a chain of dependent loads on few lanes, the drift streams rows:
+// together they take as long as the longer (7 us and 7 us apart at 16 replicas).
+__global__ __launch_bounds__(kBlock) void k_kick_sample_batch(const KickDriftArgs *__restrict__ kick,
+                                                              const SampleArgs *__restrict__ samp,
+                                                              const EnsItem *__restrict__ items, const uint64_t *shift)
 {
-    if (!tab || !items || n < 1 || !shift) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sample_batch, dim3(n), dim3(kSampleThreads), 0, st, tab, items, shift);
+    const EnsItem e = items[blockIdx.x];
+    if (e.b < 0) sample_body(samp[e.r], (int64_t)(~e.b) * kBlock + threadIdx.x, *shift);   // uniform per workgroup
+    else kick_drift_body(kick[e.r], e.b);
+}
+
+hipError_t launch_kick_sample_batch(const KickDriftArgs *kick, const SampleArgs *samp, const EnsItem *items, int n,
+                                    const uint64_t *shift, hipStream_t st)
+{
+    if (!kick || !samp || !items || n < 1 || !shift) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_kick_sample_batch, dim3(n), dim3(kBlock), 0, st, kick, samp, items, shift);
     return hipGetLastError();
 }
 

@@ -164,7 +164,6 @@ struct KickDriftArgs {
     const double *vscale;  // null, or a device factor the velocities take before the half-kick
 };
 hipError_t launch_kick_drift(const KickDriftArgs &a, hipStream_t st);
-hipError_t launch_kick_drift_batch(const KickDriftArgs *tab, const EnsItem *per256, int n, hipStream_t st);
 
 // --- sampling ----------------------------------------------------------------
 struct SampleArgs {
@@ -190,10 +189,11 @@ struct SampleArgs {
 };
 // i.i.d. draws, or (a.mh set) the Metropolis-Hastings chain in one workgroup
 hipError_t launch_sample(const SampleArgs &a, hipStream_t st);
-// ensemble: items of 64 draws, ceil(P/64) per replica, nstep = 1
-// (shift: device word holding the ensemble step counter)
-hipError_t launch_sample_batch(const SampleArgs *tab, const EnsItem *items, int n, const uint64_t *shift,
-                               hipStream_t st);
+// ensemble: half-kick + drift (ceil(N/256) items per replica) and, beside it, the
+// draws of a step (items ~b of 256 draws, ceil(P/256) per replica, nstep = 1;
+// shift: device word holding the ensemble step counter)
+hipError_t launch_kick_sample_batch(const KickDriftArgs *kick, const SampleArgs *samp, const EnsItem *items, int n,
+                                    const uint64_t *shift, hipStream_t st);
 
 // --- structure factors -----------------------------------------------------------
 struct RhoArgs {
@@ -234,10 +234,8 @@ size_t rho_lds_bytes(int P, int chunk, bool mixed, bool fine);
 // the reduction: one workgroup per kRedModes adjacent samples
 constexpr int kRedModes = 4;
 __host__ __device__ inline int rho_reduce_blocks(int P) { return (P + kRedModes - 1) / kRedModes; }
-// ensemble: partials (rho_blocks items per replica, lds = the largest
-// rho_lds_bytes), then the reduction (rho_reduce_blocks items per replica)
-hipError_t launch_rho_batch(const RhoArgs *tab, const EnsItem *part_items, int npart, size_t lds, bool mixed,
-                            const EnsItem *red_items, int nred, hipStream_t st);
+// ensemble: the reductions (rho_reduce_blocks items per replica)
+hipError_t launch_rho_reduce_batch(const RhoArgs *tab, const EnsItem *items, int n, hipStream_t st);
 
 // --- near field ------------------------------------------------------------
 struct NearArgs {
@@ -305,12 +303,15 @@ constexpr int kNearHomes = kNearThreads / kNearShare;
 constexpr int kNearLanes = 1;
 __host__ __device__ inline int near_blocks(int N) { return (N + kNearHomes - 1) / kNearHomes; }
 __host__ __device__ inline int far_blocks(int N) { return (N + 63) / 64; }
-// ensemble: list builds (nlist_blocks items per replica); evaluations of the
-// replicas with `ng` Gaussians (0: any count, read at run time; 9: FP64 with
-// the polynomial Gaussian sums)
+// ensemble: list builds (nlist_blocks items per replica)
 hipError_t launch_nlist_batch(const NearArgs *tab, const EnsItem *items, int n, hipStream_t st);
-hipError_t launch_near_batch(const NearArgs *tab, const EnsItem *items, int n, int ng, bool mixed, bool energy,
-                             hipStream_t st);
+// ensemble: evaluations with energies of the replicas of one kind (near_blocks
+// items each: mixed precision, FP64 by polynomials, FP64 by exponentials) and
+// structure-factor partials (rho_blocks items ~b each, lds = the largest
+// rho_lds_bytes of them)
+enum class NearKind { kMixed, kPoly, kExp };
+hipError_t launch_near_batch(const NearArgs *tab, const RhoArgs *rho, const EnsItem *items, int n, NearKind kind,
+                             size_t lds, hipStream_t st);
 // Particles per structure-factor partial for a system of N particles and P samples.
 int rho_chunk(int N, int P);
 // The same when the partials run in the near launch's first workgroups (>= rho_chunk).
@@ -357,8 +358,10 @@ struct FarArgs {
 // 940 and 926; 1e6: 1 538 and 1 508 us a step.
 constexpr int kFarPairN = 450000;
 hipError_t launch_far(const FarArgs &a, hipStream_t st);
-// ensemble: far_blocks items per replica
-hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, hipStream_t st);
+// ensemble: far_blocks items per replica; advance (nullable): a step counter the
+// launch moves on (its last reader before it is the draws, the next the energies)
+hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, uint64_t *advance,
+                            hipStream_t st);
 
 // --- energies ---------------------------------------------------------------
 // An energy row: U_N, U*_F, U_k0, U_self, U_bg, KE, W_N, W*_F.
@@ -377,7 +380,8 @@ struct EnergyArgs {
     const double *ke_set;      // null, or [rows] kinetic energies to report (a global bath's, after its half-step)
 };
 hipError_t launch_energy(const EnergyArgs &a, hipStream_t st);
-// ensemble: one item per replica; each writes row *shift + row0 of its out
+// ensemble: one item per replica; each writes row *shift - 1 + row0 of its out
+// (the far field has moved the counter on)
 hipError_t launch_energy_batch(const EnergyArgs *tab, const EnsItem *items, int n, const uint64_t *shift,
                                hipStream_t st);
 
