@@ -583,9 +583,9 @@ namespace rbsog {
 
 int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev, const double *m_dev, void *ws_dev,
                   size_t ws_bytes, hipStream_t stream, const int32_t *lattice_dev, rbsog_handle **out,
-                  const double *q_host, const double *m_host, bool sync)
+                  const Derived *derived, const double *q_host, const double *m_host, Uploads *up)
 {
-    int rc = check_params(p, s);
+    int rc = derived ? RBSOG_OK : check_params(p, s);
     if (rc) return rc;
     if (!q_dev || !m_dev || !out) return fail(RBSOG_EINVAL, "null q, m or out");
     if (!ws_dev || ((uintptr_t)ws_dev % kAlign)) return fail(RBSOG_EWORKSPACE, "workspace must be 256-byte aligned");
@@ -596,7 +596,7 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
     h->q = q_dev;
     h->m = m_dev;
     h->st = stream;
-    h->d = derive(p, s);
+    h->d = derived ? *derived : derive(p, s);
     h->g = make_geom(h->d.Lb, h->d.nc);
     h->gf = make_geom(h->d.Lb, h->d.nf);
     h->V = h->d.Lb[0] * h->d.Lb[1] * h->d.Lb[2];
@@ -647,7 +647,7 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
         return fail(RBSOG_EINVAL, "all charges are zero");
     }
     Tables t;
-    build_tables(*s, *p, q2, h->d.mmax, &t, lattice_dev == nullptr);
+    build_tables(*s, *p, q2, h->d.mmax, &t, lattice_dev == nullptr, true);
     h->nshell = t.nshell;
     h->S = t.S;
     h->ws = (char *)ws_dev;
@@ -699,24 +699,22 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
     h->cdf_q = (double *)(w + L.cdf_q);
     h->mh = (int32_t *)(w + L.mh);
     h->bath = (double *)(w + L.bath);
-    double tabh[2 * kPhaseTable];
-    phase_table(tabh);
     h->lists_valid = false;
     e = hipSuccess;
-    if (!lattice_dev)
-        e = hipMemcpyAsync(h->lattice, t.packed.data(), sizeof(int32_t) * t.packed.size(), hipMemcpyHostToDevice,
-                           h->st);
-    if (e == hipSuccess) e = hipMemcpyAsync(h->cdf, t.cdf.data(), sizeof(double) * t.nshell, hipMemcpyHostToDevice, h->st);
-    if (e == hipSuccess) e = hipMemcpyAsync(h->coef, t.coef.data(), sizeof(double) * t.nshell, hipMemcpyHostToDevice, h->st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h->first, t.shell_first.data(), sizeof(int32_t) * t.nshell, hipMemcpyHostToDevice, h->st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h->size, t.shell_size.data(), sizeof(int32_t) * t.nshell, hipMemcpyHostToDevice, h->st);
-    if (e == hipSuccess) e = hipMemcpyAsync(h->tab, tabh, sizeof(tabh), hipMemcpyHostToDevice, h->st);
-    std::vector<double> tabf(2 * (size_t)kFarTable);
-    far_table(tabf.data());
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h->tab_far, tabf.data(), sizeof(double) * tabf.size(), hipMemcpyHostToDevice, h->st);
+    auto put = [&](void *dst, const void *src, size_t bytes) {
+        if (e != hipSuccess || bytes == 0) return;
+        e = up ? up->copy(dst, src, bytes) : hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, h->st);
+    };
+    auto clear = [&](void *dst, size_t bytes) {
+        if (e == hipSuccess) e = up ? up->fill(dst, bytes, kCopyZero) : hipMemsetAsync(dst, 0, bytes, h->st);
+    };
+    if (!lattice_dev) put(h->lattice, t.packed.data(), sizeof(int32_t) * t.packed.size());
+    put(h->cdf, t.cdf.data(), sizeof(double) * t.nshell);
+    put(h->coef, t.coef.data(), sizeof(double) * t.nshell);
+    put(h->first, t.shell_first.data(), sizeof(int32_t) * t.nshell);
+    put(h->size, t.shell_size.data(), sizeof(int32_t) * t.nshell);
+    put(h->tab, phase_table(), sizeof(double) * 2 * kPhaseTable);
+    put(h->tab_far, far_table(), sizeof(double) * 2 * kFarTable);
     // Metropolis-Hastings draws: the proposal measure's CDF (F = 1) over the
     // same shells, and an empty chain
     std::vector<double> cdfq;
@@ -729,22 +727,18 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
         if (tq.nshell != t.nshell) e = hipErrorInvalidValue;   // both list the shells with r3(m) > 0
         cdfq = tq.cdf;
         h->Sq = tq.S;
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->cdf_q, cdfq.data(), sizeof(double) * cdfq.size(), hipMemcpyHostToDevice, h->st);
-        if (e == hipSuccess) e = hipMemcpyAsync(h->mh, mh0, sizeof(mh0), hipMemcpyHostToDevice, h->st);
+        put(h->cdf_q, cdfq.data(), sizeof(double) * cdfq.size());
+        put(h->mh, mh0, sizeof(mh0));
     }
     static const double bath0[kBathWords] = {};
-    if (e == hipSuccess) e = hipMemcpyAsync(h->bath, bath0, sizeof(bath0), hipMemcpyHostToDevice, h->st);
+    put(h->bath, bath0, sizeof(bath0));
     double fabh[2 * kMaxGauss] = {};
     for (int g = 0; g < s->n; ++g) {
         fabh[g] = s->A[g];
         fabh[kMaxGauss + g] = s->B[g];
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(h->fab, fabh, sizeof(fabh), hipMemcpyHostToDevice, h->st);
-    std::vector<double> vmh((size_t)h->d.mmax + 1);
-    virial_table(*s, p->L, h->d.mmax, vmh.data());
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h->vm, vmh.data(), sizeof(double) * vmh.size(), hipMemcpyHostToDevice, h->st);
+    put(h->fab, fabh, sizeof(fabh));
+    put(h->vm, t.vm.data(), sizeof(double) * t.vm.size());
     // full lattice: every n with its coefficient Fhat(k^2)/V, k = 2 pi n / L
     std::vector<double> full;
     if (e == hipSuccess && h->d.full_k) {
@@ -759,15 +753,14 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
             full[4 * i + 2] = nz;
             full[4 * i + 3] = fhat(*s, box_k2(h->d.Lb, nx, ny, nz)) / V;
         }
-        e = hipMemcpyAsync(h->samp, full.data(), sizeof(double) * full.size(), hipMemcpyHostToDevice, h->st);
+        put(h->samp, full.data(), sizeof(double) * full.size());
     }
-    if (e == hipSuccess) e = hipMemsetAsync(h->flag, 0, sizeof(int32_t) * 8, h->st);
-    if (e == hipSuccess) e = hipMemsetAsync(h->count, 0, L.cell_start - L.count, h->st);
-    if (e == hipSuccess) e = launch_iota(h->order, (int)p->N, h->st);   // a cell order before the first build
-    // the uploads above are from host memory this function releases: pageable
-    // copies are staged by the runtime before the calls return, so only the
-    // single-system path's documented synchronisation remains
-    if (e == hipSuccess && sync) e = hipStreamSynchronize(h->st);
+    clear(h->flag, sizeof(int32_t) * 8);
+    clear(h->count, L.cell_start - L.count);
+    if (e == hipSuccess)   // a cell order before the first build
+        e = up ? up->fill(h->order, sizeof(int32_t) * (size_t)p->N, kCopyIota) : launch_iota(h->order, (int)p->N, h->st);
+    // the uploads above are from host memory this function releases
+    if (e == hipSuccess && !up) e = hipStreamSynchronize(h->st);
     if (e != hipSuccess) {
         delete h;
         return fail(RBSOG_EHIP, "uploading tables: %s", hipGetErrorString(e));

@@ -59,6 +59,7 @@ struct Tables {
     std::vector<double> coef;          // [nshell] S / (P V F(k^2))
     std::vector<int32_t> shell_first;  // [nshell] index of the shell's first point
     std::vector<int32_t> shell_size;   // [nshell] points in the shell, r3(m)
+    std::vector<double> vm;            // [mmax + 1] k^2 G / Fhat at |n|^2 = m, when asked for
 };
 
 int default_mmax(const rbsog_sog &s, double L);
@@ -72,13 +73,13 @@ void lattice_copy(int mmax, int32_t *out);
 double density(int kind, double kT, double V, double Q2, const KernelTerms &K, double k2);
 // Fhat(k^2) = sum_m A_m exp(-B_m k^2) in ascending m
 double fhat(const rbsog_sog &s, double k2);
-// vm[m] = k^2 G(k^2) / Fhat(k^2) at k^2 = (2 pi / L)^2 m, m = 0 .. mmax, with
-// G = -dFhat/d(k^2): the factor a mode's term of the far-field virial carries
-// beside 3/2 of its energy term
-void virial_table(const rbsog_sog &s, double L, int mmax, double *vm);
 // shell CDF, coefficients and shell ranges; the packed lattice too when asked
-// (a cuboid box, see box_edges, gets one entry per lattice point and ignores mmax)
-void build_tables(const rbsog_sog &s, const rbsog_params &p, double Q2, int mmax, Tables *t, bool with_lattice);
+// (a cuboid box, see box_edges, gets one entry per lattice point and ignores mmax).
+// with_virial: also vm[m] = k^2 G(k^2) / Fhat(k^2) at k^2 = (2 pi / L)^2 m of the
+// shells, with G = -dFhat/d(k^2): the factor a mode's term of the far-field virial
+// carries beside 3/2 of its energy term
+void build_tables(const rbsog_sog &s, const rbsog_params &p, double Q2, int mmax, Tables *t, bool with_lattice,
+                  bool with_virial = false);
 // k^2 of lattice point n in a box of edges Lb
 double box_k2(const double Lb[3], int nx, int ny, int nz);
 // points of a cuboid's lattice (every n != 0 with Fhat(k^2) >= 1e-16 Fhat(0)), or -1 beyond |n_d| = 511
@@ -86,12 +87,12 @@ int64_t box_lattice_points(const rbsog_sog &s, const double Lb[3]);
 // the box edges of the parameters (Ly, Lz of 0 take L)
 void box_edges(const rbsog_params *p, double Lb[3]);
 // (sin, cos)(2 pi j / kPhaseTable), j = 0 .. kPhaseTable - 1, interleaved, from
-// the host's libm: the rotation table of the FP64 phase kernels
+// the host's libm: the rotation table of the FP64 phase kernels (2 * kPhaseTable words)
 constexpr int kPhaseTable = 128;
-void phase_table(double out[2 * kPhaseTable]);
+const double *phase_table();
 // the far field's finer table, (sin, cos)(2 pi j / 1024)
 constexpr int kFarTable = 1024;
-void far_table(double out[2 * kFarTable]);
+const double *far_table();
 // sum q and sum q^2 in particle order (plain FP64 additions, no contraction)
 void charge_sums(const double *q, int64_t N, double *q1, double *q2);
 

@@ -442,6 +442,45 @@ __global__ __launch_bounds__(kBlock) void k_iota(int32_t *order, int N)
     if (p < N) order[p] = p;
 }
 
+// Piece blockIdx.y.  A replica's state, tables and argument blocks are some 16
+// pieces of 4 bytes to megabytes: one launch over PCIe in place of as many copies,
+// each of which costs the host more (4 us) than its bytes cost the link.
+__global__ __launch_bounds__(kBlock) void k_copy_segs(CopySegs a)
+{
+    const CopySeg s = a.s[blockIdx.y];
+    const uint32_t t = blockIdx.x * kBlock + threadIdx.x, step = gridDim.x * kBlock, words = s.bytes / 4;
+    uint32_t *dst = (uint32_t *)s.dst;
+    if (s.kind == kCopyIota) {
+        for (uint32_t i = t; i < words; i += step) dst[i] = i;
+        return;
+    }
+    const uint32_t *src = (const uint32_t *)s.src;
+    uint32_t quads = 0;
+    if ((((uintptr_t)s.src | (uintptr_t)s.dst) & 15) == 0) {
+        quads = words / 4;
+        const uint4 zero = {0, 0, 0, 0};
+        for (uint32_t i = t; i < quads; i += step)
+            ((uint4 *)s.dst)[i] = s.kind == kCopyZero ? zero : ((const uint4 *)s.src)[i];
+    }
+    for (uint32_t i = 4 * quads + t; i < words; i += step) dst[i] = s.kind == kCopyZero ? 0u : src[i];
+}
+
+hipError_t launch_copy_segs(const CopySegs &a, hipStream_t st)
+{
+    if (a.n < 1 || a.n > kCopySegs) return hipErrorInvalidValue;
+    uint32_t most = 0;
+    for (int i = 0; i < a.n; ++i) {
+        const CopySeg &s = a.s[i];
+        if (!s.dst || s.bytes == 0 || (s.bytes & 3) || ((uintptr_t)s.dst & 3) ||
+            (s.kind == kCopyWords && (!s.src || ((uintptr_t)s.src & 3))) || s.kind < kCopyWords || s.kind > kCopyIota)
+            return hipErrorInvalidValue;
+        most = s.bytes > most ? s.bytes : most;
+    }
+    const uint32_t blocks = (most + 16 * kBlock - 1) / (16 * kBlock);   // 16 bytes a lane and turn
+    hipLaunchKernelGGL(k_copy_segs, dim3(blocks < 256 ? blocks : 256, a.n), dim3(kBlock), 0, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_iota(int32_t *order, int N, hipStream_t st)
 {
     if (!order || N < 1) return hipErrorInvalidValue;

@@ -116,6 +116,22 @@ hipError_t launch_cell_build(const CellArgs &a, hipStream_t st);
 hipError_t launch_cell_build_batch(const CellArgs *tab, const EnsItem *per256, int n256, const EnsItem *pertile,
                                    int ntile, hipStream_t st);
 hipError_t launch_set_int(int32_t *p, int32_t v, hipStream_t st);
+// Up to kCopySegs pieces moved by one launch: copies (src may be pinned host
+// memory), words set to zero, words set to their index.  Addresses and sizes are
+// multiples of 4 bytes.
+constexpr int kCopySegs = 24;
+enum CopyKind : int32_t { kCopyWords, kCopyZero, kCopyIota };
+struct CopySeg {
+    const void *src;
+    void *dst;
+    uint32_t bytes;
+    int32_t kind;
+};
+struct CopySegs {
+    int n;
+    CopySeg s[kCopySegs];
+};
+hipError_t launch_copy_segs(const CopySegs &a, hipStream_t st);
 // order[p] = p (a valid cell order before the first build)
 hipError_t launch_iota(int32_t *order, int N, hipStream_t st);
 

@@ -41,9 +41,7 @@ int scratch_ptr(char **out)
         void *p = nullptr;
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return fail(RBSOG_EHIP, "hipGetSymbolAddress: %s", hipGetErrorString(e));
-        double tab[2 * kPhaseTable];
-        phase_table(tab);
-        e = hipMemcpy(p, tab, sizeof(tab), hipMemcpyHostToDevice);
+        e = hipMemcpy(p, phase_table(), sizeof(double) * 2 * kPhaseTable, hipMemcpyHostToDevice);
         if (e != hipSuccess) return fail(RBSOG_EHIP, "rotation table: %s", hipGetErrorString(e));
         g_ptr[dev] = (char *)p;
     }

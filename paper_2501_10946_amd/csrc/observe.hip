@@ -380,9 +380,7 @@ extern "C" int rbsog_ssf(int64_t N, double L, const double *x_dev, const double 
         start[(size_t)(nx * nx + ny * ny + nz * nz) + 1] += 1;
     }
     for (int m = 1; m <= m_s + 1; ++m) start[(size_t)m] += start[(size_t)m - 1];
-    double tab[2 * kPhaseTable];
-    phase_table(tab);
-    HIPCHECK(hipMemcpyAsync(s + pl.o_tab, tab, sizeof(tab), hipMemcpyHostToDevice, st));
+    HIPCHECK(hipMemcpyAsync(s + pl.o_tab, phase_table(), sizeof(double) * 2 * kPhaseTable, hipMemcpyHostToDevice, st));
     if (pl.K > 0)
         HIPCHECK(hipMemcpyAsync(s + pl.o_modes, modes.data(), sizeof(double) * modes.size(), hipMemcpyHostToDevice, st));
     HIPCHECK(hipMemcpyAsync(s + pl.o_start, start.data(), sizeof(int64_t) * start.size(), hipMemcpyHostToDevice, st));

@@ -182,14 +182,34 @@ bool adapt_skin(rbsog_handle *h, double dt);
 // more than half their steps (read back without waiting; checked when the
 // count of a previous call has arrived).
 bool adapt_skin_rebuilds(rbsog_handle *h);
+// Host arrays on their way to the device: copied into pinned memory, from where
+// one kernel per flush (on the stream st) moves all of them, with the fills that
+// go along.  What does not fit goes by hipMemcpyAsync from where it lies, and the
+// flush then waits for the stream.  The pinned memory may be filled again (reset)
+// once the kernel of the last flush is done.
+struct Uploads {
+    hipStream_t st = nullptr;
+    hipEvent_t done = nullptr;   // recorded by each flush
+    char *host = nullptr;        // pinned, read by the device at this address
+    size_t cap = 0, used = 0;
+    CopySegs segs{};
+    bool direct = false;
+    // waits until the device has read what the last flush sent, then starts again
+    hipError_t reset();
+    hipError_t copy(void *dst, const void *src, size_t bytes);
+    hipError_t fill(void *dst, size_t bytes, int32_t kind);   // kCopyZero or kCopyIota
+    hipError_t flush();
+};
 // rbsog_create; with lattice_dev (the packed lattice up to at least the
 // system's m_max, owned by the caller) the workspace holds no lattice copy
+// derived (nullable): derive(p, s) of parameters that check_params has passed.
 // q_host, m_host (nullable): host copies of the charges and masses, which
-// spare the read-back of q_dev and m_dev; with sync false nothing waits on the
-// stream (the table uploads complete in stream order).
+// spare the read-back of q_dev and m_dev.  up (nullable): takes the uploads in
+// place of copies on the stream, which are then waited for.
 int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev, const double *m_dev, void *ws_dev,
                   size_t ws_bytes, hipStream_t stream, const int32_t *lattice_dev, rbsog_handle **out,
-                  const double *q_host = nullptr, const double *m_host = nullptr, bool sync = true);
+                  const Derived *derived = nullptr, const double *q_host = nullptr, const double *m_host = nullptr,
+                  Uploads *up = nullptr);
 // gate_raise non-null (with kick): the far kernel also applies the next
 // step's first half-kick and drift, raising gate_raise; gate_clear is cleared
 // the thermostat of a step's drift into force index `step` (off without friction)
