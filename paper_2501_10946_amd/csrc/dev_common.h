@@ -317,6 +317,13 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
     const double2 *col = a.part + (live ? l : 0);
     const size_t P = (size_t)a.P;
     const int nch = live ? a.nchunk : 0;
+    // what the finishing threads need besides is on its way with the partials, and
+    // the last of those all together: at small sizes the launch is a chain of
+    // loads that wait for one another (N = 10 007, P = 193, mixed: a step 30.4 ->
+    // 29.9 us; N = 60 000, P = 500: 87 -> 86)
+    const bool last = t < kRedModes && live;
+    double4 sl{};
+    if (last) sl = a.samp[l];
     double re = 0.0, im = 0.0;
     int c = c0;
     for (; c + 3 * kLanes < nch; c += 4 * kLanes) {
@@ -331,11 +338,15 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
         re += v3.x;
         im += v3.y;
     }
-    for (; c < nch; c += kLanes) {
-        double2 v = col[(size_t)c * P];
-        re += v.x;
-        im += v.y;
+    double2 v[3];   // up to three more, all in flight
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = c + k * kLanes < nch ? col[(size_t)(c + k * kLanes) * P] : double2{0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        re += v[k].x;   // + 0 past the last group
+        im += v[k].y;
     }
+    const double vm = last && a.eW ? mode_vm(a, sl) : 0.0;
 #pragma unroll
     for (int off = 32; off >= kRedModes; off >>= 1) {
         re += __shfl_xor(re, off);
@@ -343,7 +354,7 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
     }
     if ((t & 63) < kRedModes) red[t >> 6][m] = make_double2(re, im);
     __syncthreads();
-    if (t < kRedModes && live) {
+    if (last) {
         re = 0.0;
         im = 0.0;
 #pragma unroll
@@ -351,13 +362,13 @@ __device__ inline void rho_reduce_body(const RhoArgs &a, int b)
             re += red[w][t].x;
             im += red[w][t].y;
         }
-        double cf = a.samp[l].w;
+        const double cf = sl.w;
         a.rho[l] = make_double2(re, im);
         if (a.gk) {   // a step's modes: the far field's coefficients and the energies
             a.gk[l] = far_coef(a.mixed, cf, re, im);
             a.eF[l] = 0.5 * cf * (re * re + im * im);
         }
-        if (a.eW) a.eW[l] = cf * (re * re + im * im) * (1.5 - mode_vm(a, a.samp[l]));
+        if (a.eW) a.eW[l] = cf * (re * re + im * im) * (1.5 - vm);
         if (a.rho_out) {
             a.rho_out[2 * l] = re;
             a.rho_out[2 * l + 1] = im;
