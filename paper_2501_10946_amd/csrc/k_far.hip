@@ -9,15 +9,18 @@ namespace rbsog {
 // far field of the random batch (eq. UF):
 //   f_i += -q_i (2 pi / L) sum_l coef_l n_l Im(exp(-i k_l . r_i) rho_l).
 // A workgroup owns 64 consecutive particles (cell order), or 128 (PPL particles
-// per lane), and has 4 waves; wave g takes the samples l = g mod 4 of each LDS
-// tile of 256 samples, so every particle's sum is spread over 4 lanes.  The 4
-// partial sums are added in a fixed order, then near + far is written (in cell
-// order, and/or in the caller's order) and the second half-kick applied in cell
-// order; in a run of steps the next step's first half-kick and drift follow at
-// once.  Two particles per lane share the LDS reads of a mode (bound beside the
-// arithmetic otherwise) and give each wave two independent chains more; a
-// system whose workgroups would then fill the chip less than a few times over
-// keeps one.
+// per lane), and has W waves with C chains each; chain c of wave g takes the
+// samples l = g + W c mod W C of each LDS tile of 256 samples, so every particle's
+// sum is spread over W lanes.  The partial sums are added in a fixed order, then
+// near + far is written (in cell order, and/or in the caller's order) and the
+// second half-kick applied in cell order; in a run of steps the next step's first
+// half-kick and drift follow at once.  Two particles per lane share the LDS reads
+// of a mode (bound beside the arithmetic otherwise) and give each wave two
+// independent chains more, with W C = 4; a system whose workgroups would then
+// fill the chip less than a few times over keeps one, and W C = 16 instead: its
+// waves are few, and more waves or more chains in each hide more of what an
+// instruction waits (N = 10 007, P = 193, mixed, a step with a thermostat: 29.9 ->
+// 28.9 us; N = 6e4, P = 500, mixed: 86 -> 85; N = 2e5, P = 300, FP64: 195.6 -> 194.9).
 //
 // Bound by its vector instructions, 20 per (particle, mode) in FP64: three FMAs of
 // the phase (which start from the mode's offset), 13 of the cosine, three to
@@ -29,9 +32,8 @@ namespace rbsog {
 // the FP64 vector unit for as long as the FMAs they replace.
 // ---------------------------------------------------------------------------
 
-constexpr int kFarGroups = 4;
-constexpr int kFarThreads = 64 * kFarGroups;
 constexpr int kFarTile = 256;
+constexpr int kFarThreads = 256;   // the ensemble's workgroups
 
 // A tile's samples in LDS: k = (n, phase offset) and w = -size n (FP64), or k =
 // (n, coef) and w.xy = coef rho (mixed).
@@ -63,19 +65,47 @@ __device__ inline void far_add(const FarArgs &a, const double4 &k, const double2
     }
 }
 
-template <bool MIXED, bool DRIFT, int PPL>
+// A particle's row of what the far field adds to and moves.
+struct FarRow {
+    double fn[3], v[3], xb[3], m;
+    int order;
+};
+template <bool DRIFT>
+__device__ inline FarRow far_row(const FarArgs &a, int p)
+{
+    static_assert(kNearLanes == 1, "one partial near force per particle");
+    FarRow r{};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) r.fn[d] = a.fnear[(size_t)d * a.N + p];
+    if (a.vs) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            r.v[d] = a.vs[(size_t)d * a.N + p];
+            if (DRIFT) r.xb[d] = a.xb[(size_t)d * a.N + p];
+        }
+        r.m = a.ms[p];
+    }
+    if (a.f || a.f_near_out || (DRIFT && a.th.on)) r.order = a.order[p];
+    return r;
+}
+
+template <bool MIXED, bool DRIFT, int PPL, int W, int C>
 __device__ inline void far_body(const FarArgs &a, int b)
 {
-    __shared__ FarTile tile;
-    static_assert(sizeof(tile) >= 3 * PPL * kFarThreads * sizeof(double), "partials reuse the sample tile");
-    double(*part)[PPL * kFarThreads] = (double(*)[PPL * kFarThreads])&tile;
+    static_assert((W == 8 && C == 2) || (W == 4 && (C == 4 || C == 1)), "the orders of addition below");
+    constexpr int G = W * C;   // mode groups: wave g's chain c takes the modes l = g + W c mod G
+    constexpr int kPart = 64 * W * PPL;
+    constexpr size_t kLds = sizeof(FarTile) > 3 * kPart * sizeof(double) ? sizeof(FarTile) : 3 * kPart * sizeof(double);
+    __shared__ __align__(16) char lds[kLds];   // a tile of samples, then the waves' partials
+    FarTile &tile = *(FarTile *)lds;
+    double(*part)[kPart] = (double(*)[kPart])lds;
     const int t = threadIdx.x;
     const int g = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;   // g is uniform per wave
     if (a.gate_clear && b == 0 && t == 0) {
         if (a.rebuilds && *a.gate_clear) *a.rebuilds += 1;
         *a.gate_clear = 0;
     }
-    double s[PPL][3], acc[PPL][3];
+    double s[PPL][3], acc[C][PPL][3];
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
         const int p = (b * PPL + i) * 64 + lane;
@@ -83,11 +113,30 @@ __device__ inline void far_body(const FarArgs &a, int b)
         s[i][0] = pi.x * a.inv_L[0];
         s[i][1] = pi.y * a.inv_L[1];
         s[i][2] = pi.z * a.inv_L[2];
-        acc[i][0] = acc[i][1] = acc[i][2] = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c][i][0] = acc[c][i][1] = acc[c][i][2] = 0.0;
     }
+    // what the finishing wave reads besides the partials: in a small system it is
+    // on its way while the modes are summed (its registers cost a larger one more)
+    constexpr bool EARLY = W > 4;
+    const int p = b * PPL * 64 + t;
+    double4 pi{};
+    FarRow row{};
+    if (EARLY && g == 0 && p < a.N) {
+        pi = a.xs[p];
+        row = far_row<DRIFT>(a, p);
+    }
+    // chain c adds mode m of the tile to the wave's particles
+    auto add = [&](int c, int m) {
+        const double4 k0 = tile.k[m];
+        const double2 w0 = tile.w[m];
+        const double z0 = MIXED ? 0.0 : tile.wz[m];
+#pragma unroll
+        for (int i = 0; i < PPL; ++i) far_add<MIXED>(a, k0, w0, z0, s[i], acc[c][i]);
+    };
     for (int l0 = 0; l0 < a.P; l0 += kFarTile) {
         __syncthreads();
-        if (l0 + t < a.P) {
+        if (t < kFarTile && l0 + t < a.P) {
             const double4 k = a.samp[l0 + t];
             const double2 gk = a.gk[l0 + t];
             if (MIXED) {
@@ -101,51 +150,67 @@ __device__ inline void far_body(const FarArgs &a, int b)
         }
         __syncthreads();
         int nl = min(kFarTile, a.P - l0);
-        // two modes per pass (independent chains), added in mode order
         int m = g;
-        for (; m + kFarGroups < nl; m += 2 * kFarGroups) {
-            const double4 k0 = tile.k[m], k1 = tile.k[m + kFarGroups];
-            const double2 w0 = tile.w[m], w1 = tile.w[m + kFarGroups];
-            const double z0 = MIXED ? 0.0 : tile.wz[m], z1 = MIXED ? 0.0 : tile.wz[m + kFarGroups];
+        if constexpr (C == 1) {
+            // two modes per pass (independent chains), added in mode order
+            for (; m + W < nl; m += 2 * W) {
+                const double4 k0 = tile.k[m], k1 = tile.k[m + W];
+                const double2 w0 = tile.w[m], w1 = tile.w[m + W];
+                const double z0 = MIXED ? 0.0 : tile.wz[m], z1 = MIXED ? 0.0 : tile.wz[m + W];
 #pragma unroll
-            for (int i = 0; i < PPL; ++i) {
-                far_add<MIXED>(a, k0, w0, z0, s[i], acc[i]);
-                far_add<MIXED>(a, k1, w1, z1, s[i], acc[i]);
+                for (int i = 0; i < PPL; ++i) {
+                    far_add<MIXED>(a, k0, w0, z0, s[i], acc[0][i]);
+                    far_add<MIXED>(a, k1, w1, z1, s[i], acc[0][i]);
+                }
             }
-        }
-        if (m < nl) {
-            const double4 k0 = tile.k[m];
-            const double2 w0 = tile.w[m];
-            const double z0 = MIXED ? 0.0 : tile.wz[m];
+            if (m < nl) add(0, m);
+        } else {
+            for (; m + W * (C - 1) < nl; m += G) {
 #pragma unroll
-            for (int i = 0; i < PPL; ++i) far_add<MIXED>(a, k0, w0, z0, s[i], acc[i]);
+                for (int c = 0; c < C; ++c) add(c, m + W * c);
+            }
+#pragma unroll
+            for (int c = 0; c < C - 1; ++c)
+                if (m + W * c < nl) add(c, m + W * c);
         }
     }
     __syncthreads();   // the sample tile is done with: it holds the partials next
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
-        const int at = (g * PPL + i) * 64 + lane;   // group g's partial of particle (i, lane)
-        part[0][at] = acc[i][0];
-        part[1][at] = acc[i][1];
-        part[2][at] = acc[i][2];
+        const int at = (g * PPL + i) * 64 + lane;   // wave g's partial of particle (i, lane)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if constexpr (C == 1) part[d][at] = acc[0][i][d];
+            else if constexpr (C == 2) part[d][at] = acc[0][i][d] + acc[1][i][d];
+            else part[d][at] = (acc[0][i][d] + acc[2][i][d]) + (acc[1][i][d] + acc[3][i][d]);
+        }
     }
     __syncthreads();
     if (t >= 64 * PPL) return;   // whole waves; thread t finishes particle t
-    const int p = b * PPL * 64 + t;
     double ke = 0.0;
     if (p < a.N) {
-        const double4 pi = a.xs[p];
+        if (!EARLY) {
+            pi = a.xs[p];
+            row = far_row<DRIFT>(a, p);
+        }
         double bx = 0.0, by = 0.0, bz = 0.0;
+        // of 16 groups, (k + k8) + (k4 + k12) for k = 0 .. 3, then these four: the same
+        // order whether eight waves or four held them
 #pragma unroll
-        for (int k = 0; k < kFarGroups; ++k) {
-            bx += part[0][k * 64 * PPL + t];
-            by += part[1][k * 64 * PPL + t];
-            bz += part[2][k * 64 * PPL + t];
+        for (int k = 0; k < 4; ++k) {
+            double sx = part[0][k * 64 * PPL + t], sy = part[1][k * 64 * PPL + t], sz = part[2][k * 64 * PPL + t];
+            if constexpr (W == 8) {
+                sx += part[0][(k + 4) * 64 * PPL + t];
+                sy += part[1][(k + 4) * 64 * PPL + t];
+                sz += part[2][(k + 4) * 64 * PPL + t];
+            }
+            bx += sx;
+            by += sy;
+            bz += sz;
         }
         const double scx = -pi.w * a.two_pi_over_L[0], scy = -pi.w * a.two_pi_over_L[1];
         const double scz = -pi.w * a.two_pi_over_L[2];
-        static_assert(kNearLanes == 1, "one partial near force per particle");
-        const double fnx = a.fnear[p], fny = a.fnear[a.N + p], fnz = a.fnear[2 * (size_t)a.N + p];
+        const double fnx = row.fn[0], fny = row.fn[1], fnz = row.fn[2];
         double fx = fnx + scx * bx, fy = fny + scy * by, fz = fnz + scz * bz;
         if (a.fs) {
             a.fs[p] = fx;
@@ -153,7 +218,7 @@ __device__ inline void far_body(const FarArgs &a, int b)
             a.fs[2 * a.N + p] = fz;
         }
         if (a.f || a.f_near_out) {
-            int i = a.order[p];
+            const int i = row.order;
             if (a.f) {
                 a.f[i] = fx;
                 a.f[a.N + i] = fy;
@@ -167,16 +232,16 @@ __device__ inline void far_body(const FarArgs &a, int b)
         }
         raise_any(a.flag, !isfinite(fx + fy + fz));
         if (a.vs) {
-            double mi = a.ms[p];
+            double mi = row.m;
             double hm = a.half_dt / mi;
-            double vx = a.vs[p] + hm * fx, vy = a.vs[a.N + p] + hm * fy, vz = a.vs[2 * a.N + p] + hm * fz;
+            double vx = row.v[0] + hm * fx, vy = row.v[1] + hm * fy, vz = row.v[2] + hm * fz;
             ke = 0.5 * mi * (vx * vx + vy * vy + vz * vz);
             if (DRIFT) {   // the next step's first half-kick and drift
                 double x[3] = {pi.x, pi.y, pi.z}, v[3] = {vx, vy, vz};
                 const double f[3] = {fx, fy, fz};
                 bool bad = false;
-                double d2 = kick_drift_row(x, v, f, hm, a.dt, a.L, a.inv_L, a.xb, a.N, p, &bad, a.th,
-                                           a.th.on ? (uint64_t)a.order[p] : 0, mi);
+                double d2 = kick_drift_row(x, v, f, hm, a.dt, a.L, a.inv_L, row.xb, 1, 0, &bad, a.th,
+                                           (uint64_t)row.order, mi);
                 vx = v[0];
                 vy = v[1];
                 vz = v[2];
@@ -196,10 +261,10 @@ __device__ inline void far_body(const FarArgs &a, int b)
     }
 }
 
-template <bool MIXED, bool DRIFT, int PPL>
-__global__ __launch_bounds__(kFarThreads) void k_far(FarArgs a)
+template <bool MIXED, bool DRIFT, int PPL, int W, int C>
+__global__ __launch_bounds__(64 * W) void k_far(FarArgs a)
 {
-    far_body<MIXED, DRIFT, PPL>(a, (int)blockIdx.x);
+    far_body<MIXED, DRIFT, PPL, W, C>(a, (int)blockIdx.x);
 }
 
 template <bool MIXED>
@@ -208,7 +273,10 @@ __global__ __launch_bounds__(kFarThreads) void k_far_batch(const FarArgs *__rest
 {
     const EnsItem e = items[blockIdx.x];
     if (advance && blockIdx.x == 0 && threadIdx.x == 0) *advance += 1;
-    far_body<MIXED, false, 1>(tab[e.r], e.b);
+    const FarArgs &a = tab[e.r];
+    // the order of the system alone
+    if (a.N < kFarPairN) far_body<MIXED, false, 1, 4, 4>(a, e.b);
+    else far_body<MIXED, false, 1, 4, 1>(a, e.b);
 }
 
 hipError_t launch_far_batch(const FarArgs *tab, const EnsItem *items, int n, bool mixed, uint64_t *advance,
@@ -224,8 +292,9 @@ template <bool MIXED, bool DRIFT>
 static void launch_far_as(const FarArgs &a, hipStream_t st)
 {
     const int nb = far_blocks(a.N);
-    if (a.N >= kFarPairN) hipLaunchKernelGGL((k_far<MIXED, DRIFT, 2>), dim3((nb + 1) / 2), dim3(kFarThreads), 0, st, a);
-    else hipLaunchKernelGGL((k_far<MIXED, DRIFT, 1>), dim3(nb), dim3(kFarThreads), 0, st, a);
+    if (a.N >= kFarPairN) hipLaunchKernelGGL((k_far<MIXED, DRIFT, 2, 4, 1>), dim3((nb + 1) / 2), dim3(256), 0, st, a);
+    else if (a.N >= kFarWideN) hipLaunchKernelGGL((k_far<MIXED, DRIFT, 1, 4, 4>), dim3(nb), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_far<MIXED, DRIFT, 1, 8, 2>), dim3(nb), dim3(512), 0, st, a);
 }
 
 hipError_t launch_far(const FarArgs &a, hipStream_t st)

@@ -373,6 +373,11 @@ struct FarArgs {
 // chip holds ~1 800: a second round that is nearly empty); 4e5: 757 and 768; 5e5:
 // 940 and 926; 1e6: 1 538 and 1 508 us a step.
 constexpr int kFarPairN = 450000;
+// systems of fewer than kFarWideN particles (two workgroups per compute unit):
+// eight waves per 64 particles, else four.  N = 10 007, P = 193, mixed, a step:
+// 29.1 us with eight, 29.6 with four (30.1 with four of one chain each); N = 5e4,
+// P = 200: 57.2 and 55.7.  Sixteen waves: 29.1 and 62.4.
+constexpr int kFarWideN = 32768;
 hipError_t launch_far(const FarArgs &a, hipStream_t st);
 // ensemble: far_blocks items per replica; advance (nullable): a step counter the
 // launch moves on (its last reader before it is the draws, the next the energies)
