@@ -132,7 +132,7 @@ Layout make_layout(int64_t N, const Derived &d, int P, bool shared_lattice)
     L.order_old = take(sizeof(int32_t) * (size_t)N);
     L.xs = take(sizeof(double) * 4 * (size_t)N);
     L.xs_old = take(sizeof(double) * 4 * (size_t)N);
-    L.tile_sum = take(sizeof(int32_t) * (size_t)scan_tiles(ncell));
+    L.tile_sum = take(sizeof(int32_t) * kTilePad * (size_t)scan_tiles(ncell));
     L.xb = take(sizeof(double) * 3 * (size_t)N);
     L.vs = take(sizeof(double) * 3 * (size_t)N);
     L.vs_old = take(sizeof(double) * 3 * (size_t)N);
@@ -757,6 +757,7 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
     }
     clear(h->flag, sizeof(int32_t) * 8);
     clear(h->count, L.cell_start - L.count);
+    clear(h->tile_sum, L.xb - L.tile_sum);
     if (e == hipSuccess)   // a cell order before the first build
         e = up ? up->fill(h->order, sizeof(int32_t) * (size_t)p->N, kCopyIota) : launch_iota(h->order, (int)p->N, h->st);
     // the uploads above are from host memory this function releases

@@ -24,38 +24,36 @@ namespace rbsog {
 __device__ inline bool gate_open(const int32_t *gate) { return gate == nullptr || *gate != 0; }
 
 // ---------------------------------------------------------------------------
-// cell list: ids + counts, scan, scatter, stable rank + gather
+// cell list: ids + counts + chains, scan, stable rank + move.  Three launches: a
+// gated step runs them all with the gate closed, each for its launch alone, and a
+// build of up to 1e5 particles is bound by them too.  Two more (a pass of its own
+// for the sums of the scan's tiles, a scatter of the members into their cells) took
+// 20 steps of N = 1e5 from 1437 to 1500 us, an evaluation of N = 5003 from 55 to
+// 62; at N = 1e6 the chains' atomics cost what the launches save (82 and 82 us a
+// build).
 // ---------------------------------------------------------------------------
 
 // Every kernel body takes its argument block and its workgroup index b within
 // the system's grid; the single-system kernels pass blockIdx.x, the ensemble
 // kernels the (replica, block) item of a work list.
 
-// Wave-aggregated counting: the particles of a wave are consecutive rows of
-// the cell order, so runs of neighbouring lanes share a cell.  The first lane
-// of each run (live lanes form a prefix of the wave) adds the run's length
-// with one atomic, and with want_base its lanes get consecutive slots from
-// the value it read back: a quarter of the atomics of one per particle at
-// ~4 particles per cell.  The slots within a cell depend on the order the
-// atomics land in, as before; the rank pass makes the final order
-// independent of them.
-__device__ inline int add_runs(int32_t *cnt, int id, bool live, bool want_base)
+// The particles of a wave are consecutive rows of the cell order before the
+// build, so neighbouring lanes mostly share a cell.  run_length: the length of
+// the run of equal ids that starts at this lane (live lanes form a prefix of the
+// wave; at most kRunMax lanes), 0 where none starts.
+constexpr int kRunBits = 5, kRunMax = 1 << kRunBits;
+constexpr uint32_t kRunRow = (1u << (32 - kRunBits)) - 1u;   // a run: its first row, and its length - 1 above
+
+__device__ inline int run_length(int id, bool live)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t lv = __builtin_amdgcn_ballot_w64(live);
     const int prev = __shfl_up(id, 1);
-    const bool head = live && (lane == 0 || prev != id);
+    const bool head = live && ((lane & (kRunMax - 1)) == 0 || prev != id);
     const uint64_t H = __builtin_amdgcn_ballot_w64(head);
-    int base = 0;
-    if (head) {
-        const uint64_t above = H & ~((2ull << lane) - 1ull);   // (2 << 63) wraps to 0: no head above lane 63
-        const int end = above ? __ffsll((long long)above) - 1 : 64 - __clzll((long long)lv);
-        if (want_base) base = atomicAdd(&cnt[id], end - lane);
-        else atomicAdd(&cnt[id], end - lane);
-    }
-    if (!want_base) return 0;
-    const int start = 63 - __clzll((long long)(H & ((2ull << lane) - 1ull)));   // this lane's run head
-    return __shfl(base, start) + (lane - start);
+    if (!head) return 0;
+    const uint64_t above = H & ~((2ull << lane) - 1ull);   // (2 << 63) wraps to 0: no head above lane 63
+    return (above ? __ffsll((long long)above) - 1 : 64 - __clzll((long long)lv)) - lane;
 }
 
 // A particle's row as it moves.
@@ -96,10 +94,18 @@ __device__ inline void cell_ids_body(const CellArgs &a, int b)
     const bool live = p < a.N;
     int id = -1;
     if (live) id = cell_id_of(a, p);
-    add_runs(a.count, id, live, false);
+    // a cell's count, and its rows as a chain of runs: the last one put in in
+    // fill[cell], the one before each in tmp[its first row] (the first points at
+    // what an earlier build left; a walk ends by the count)
+    const int n = run_length(id, live);
+    if (n > 0) {
+        atomicAdd(&a.count[id], n);
+        a.tmp[p] = (int32_t)atomicExch((uint32_t *)&a.fill[id], (uint32_t)p | ((uint32_t)(n - 1) << (32 - kRunBits)));
+    }
+    const int tile = live ? id / kScanTile : -1;
+    const int nt = run_length(tile, live);
+    if (nt > 0) atomicAdd(&a.tile_sum[tile * kTilePad], nt);
 }
-
-// Exclusive scan of the cell counts in two passes.
 
 __device__ inline int32_t block_exclusive_scan_256(int32_t v, int32_t *sh, int32_t *total)
 {
@@ -118,49 +124,16 @@ __device__ inline int32_t block_exclusive_scan_256(int32_t v, int32_t *sh, int32
     return incl - v;
 }
 
-// Pass 1: per-tile sums; the last tile to finish (a ticket counter) turns them
-// into exclusive tile offsets and resets the ticket.
-__device__ inline void scan_tiles_body(const CellArgs &a, int b)
-{
-    if (!gate_open(a.gate)) return;
-    __shared__ int32_t sh[kBlock];
-    __shared__ int last;
-    const int t = threadIdx.x;
-    const int ntiles = scan_tiles(a.g.ncell);
-    int base = b * kScanTile + t * kScanPer;
-    int32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k)
-        if (base + k < a.g.ncell) s += a.count[base + k];
-    int32_t total;
-    block_exclusive_scan_256(s, sh, &total);
-    if (t == 0) {
-        a.tile_sum[b] = total;
-        __threadfence();
-        last = atomicAdd(a.ticket, 1) == ntiles - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    // exclusive scan of the tile sums, kBlock at a time
-    int32_t run = 0;
-    for (int b0 = 0; b0 < ntiles; b0 += kBlock) {
-        int32_t v = b0 + t < ntiles ? __atomic_load_n(&a.tile_sum[b0 + t], __ATOMIC_RELAXED) : 0;
-        int32_t chunk;
-        int32_t ex = block_exclusive_scan_256(v, sh, &chunk);
-        if (b0 + t < ntiles) a.tile_sum[b0 + t] = run + ex;
-        run += chunk;
-    }
-    if (t == 0) *a.ticket = 0;
-}
-
-// Pass 2: each tile scanned with its offset; also clears the scatter's fill
-// counters and the cell counts (ready for the next build).
-__device__ inline void scan_apply_body(const CellArgs &a, int b)
+// Exclusive scan of the cell counts: each tile adds the sums of the tiles before
+// it (150 at N = 1e6) and scans its own; also clears the counts, ready for the
+// next build.
+__device__ inline void scan_body(const CellArgs &a, int b)
 {
     if (!gate_open(a.gate)) return;
     __shared__ int32_t sh[kBlock];
     int base = b * kScanTile + threadIdx.x * kScanPer;
+    int32_t before = 0;
+    for (int i = threadIdx.x; i < b; i += kBlock) before += a.tile_sum[i * kTilePad];
     int32_t c[kScanPer];
     int32_t s = 0;
 #pragma unroll
@@ -168,29 +141,18 @@ __device__ inline void scan_apply_body(const CellArgs &a, int b)
         c[k] = (base + k < a.g.ncell) ? a.count[base + k] : 0;
         s += c[k];
     }
-    int32_t total;
-    int32_t run = block_exclusive_scan_256(s, sh, &total) + a.tile_sum[b];
+    int32_t off, total;
+    (void)block_exclusive_scan_256(before, sh, &off);
+    int32_t run = block_exclusive_scan_256(s, sh, &total) + off;
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
         if (base + k < a.g.ncell) {
             a.cell_start[base + k] = run;
-            a.fill[base + k] = 0;
             a.count[base + k] = 0;
         }
         run += c[k];
     }
     if (b == 0 && threadIdx.x == 0) a.cell_start[a.g.ncell] = a.N;
-}
-
-// Unordered placement of the caller indices into each cell's segment.
-__device__ inline void scatter_body(const CellArgs &a, int b)
-{
-    if (!gate_open(a.gate)) return;
-    int p = b * kBlock + threadIdx.x;
-    const bool live = p < a.N;
-    const int c = live ? a.cell_id[p] : -1;
-    const int slot = add_runs(a.fill, c, live, true);
-    if (live) a.tmp[a.cell_start[c] + slot] = a.order_old[p];
 }
 
 // Row p of the snapshot.
@@ -220,25 +182,32 @@ __device__ inline void place_row(const CellArgs &a, const CellRow &r, int pn)
 
 // Stable position: a particle's rank within its cell is the number of cell
 // members with a smaller caller index, so the new order is that of (cell,
-// caller index) whatever order the scatter produced and whatever the old cell
-// order was.
+// caller index) whatever order the chain's runs are in and whatever the old cell
+// order was.  Also clears the tile sums.
 __device__ inline void rank_body(const CellArgs &a, int b)
 {
     if (!gate_open(a.gate)) return;
     int p = b * kBlock + threadIdx.x;
+    const int ntiles = scan_tiles(a.g.ncell), threads = (a.N + kBlock - 1) / kBlock * kBlock;
+    for (int i = p; i < ntiles; i += threads) a.tile_sum[i * kTilePad] = 0;
     if (p >= a.N) return;
     int c = a.cell_id[p];
     const int key = a.order_old[p];
-    int cb = a.cell_start[c], ce = a.cell_start[c + 1];
+    const int cb = a.cell_start[c];
     int r = 0;
-    for (int k = cb; k < ce; ++k) r += (a.tmp[k] < key);
+    uint32_t run = (uint32_t)a.fill[c];
+    for (int left = a.cell_start[c + 1] - cb;;) {
+        const int q = (int)(run & kRunRow), n = (int)(run >> (32 - kRunBits)) + 1;
+        left -= n;
+        if (left > 0) run = (uint32_t)a.tmp[q];   // on its way while this run is compared
+        for (int k = 0; k < n; ++k) r += (a.order_old[q + k] < key);
+        if (left <= 0) break;
+    }
     place_row(a, old_row(a, p), cb + r);
 }
 
 RBSOG_KERNELS(cell_ids, CellArgs, kBlock)
-RBSOG_KERNELS(scan_tiles, CellArgs, kBlock)
-RBSOG_KERNELS(scan_apply, CellArgs, kBlock)
-RBSOG_KERNELS(scatter, CellArgs, kBlock)
+RBSOG_KERNELS(scan, CellArgs, kBlock)
 RBSOG_KERNELS(rank, CellArgs, kBlock)
 
 // ---------------------------------------------------------------------------
@@ -246,10 +215,10 @@ RBSOG_KERNELS(rank, CellArgs, kBlock)
 // members of each cell and the ranks in LDS; the result is that of the passes
 // above (the same stable order).  A small system's step is a chain of short
 // launches that the host enqueues no faster than the GPU runs them (3.4 us
-// each): with its gate closed this is one of them instead of five (N = 1000: a
-// step 39 -> 28 us).  A build itself is bound by what one compute unit moves:
+// each): with its gate closed this is one of them instead of three (N = 1000: a
+// step 24 us, 32 by the passes).  A build itself is bound by what one compute unit moves:
 // up to four rows per thread stay in registers (N <= 4096); more go through the
-// snapshot, as in the passes, and take longer than those from N = 8000 on.
+// snapshot, as in the passes, and take longer than those while the gate is open.
 // ---------------------------------------------------------------------------
 
 constexpr int kSmallThreads = 1024;
@@ -349,9 +318,7 @@ hipError_t launch_cell_build(const CellArgs &a, hipStream_t st)
     int grid = (a.N + kBlock - 1) / kBlock;
     int nt = scan_tiles(a.g.ncell);
     hipLaunchKernelGGL(k_cell_ids, dim3(grid), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nt), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_scan, dim3(nt), dim3(kBlock), 0, st, a);
     hipLaunchKernelGGL(k_rank, dim3(grid), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }
@@ -361,9 +328,7 @@ hipError_t launch_cell_build_batch(const CellArgs *tab, const EnsItem *per256, i
 {
     if (!tab || (n256 > 0 && !per256) || (ntile > 0 && !pertile)) return hipErrorInvalidValue;
     if (n256 > 0) hipLaunchKernelGGL(k_cell_ids_batch, dim3(n256), dim3(kBlock), 0, st, tab, per256);
-    if (ntile > 0) hipLaunchKernelGGL(k_scan_tiles_batch, dim3(ntile), dim3(kBlock), 0, st, tab, pertile);
-    if (ntile > 0) hipLaunchKernelGGL(k_scan_apply_batch, dim3(ntile), dim3(kBlock), 0, st, tab, pertile);
-    if (n256 > 0) hipLaunchKernelGGL(k_scatter_batch, dim3(n256), dim3(kBlock), 0, st, tab, per256);
+    if (ntile > 0) hipLaunchKernelGGL(k_scan_batch, dim3(ntile), dim3(kBlock), 0, st, tab, pertile);
     if (n256 > 0) hipLaunchKernelGGL(k_rank_batch, dim3(n256), dim3(kBlock), 0, st, tab, per256);
     return hipGetLastError();
 }

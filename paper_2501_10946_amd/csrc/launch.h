@@ -14,6 +14,9 @@ namespace rbsog {
 constexpr int kBlock = 256;        // threads per workgroup of the streaming and pair kernels
 constexpr int kScanPer = 8;        // cell counts per thread of the scan
 constexpr int kScanTile = kBlock * kScanPer;
+// words from one tile's sum to the next: a memory line each (with all sums in a few
+// lines the id pass of N = 1e6 takes 240 us, so 42)
+constexpr int kTilePad = 32;
 constexpr int kRhoChunkMax = 256;  // particles per structure-factor group (at most)
 constexpr int kRhoStage = 1024;    // particles one structure-factor workgroup stages at most
 constexpr int kMaxGauss = 32;
@@ -90,26 +93,26 @@ struct CellArgs {
     double *ms_old;        // [N] snapshot of ms
     double *xb;            // SoA [3][N] positions at the build, new cell order
     int32_t *cell_id;      // [N] by current cell position
-    int32_t *count;        // [ncell]
+    int32_t *count;        // [ncell], zero between builds
     int32_t *cell_start;   // [ncell + 1]
-    int32_t *fill;         // [ncell]
-    int32_t *tmp;          // [N] caller indices of each cell's members, unordered
-    int32_t *tile_sum;     // [scan_tiles(ncell)] scan workspace
-    int32_t *ticket;       // scan's finished-tile counter: zero between builds
+    int32_t *fill;         // [ncell] the run of rows that the id pass put last into each cell
+    int32_t *tmp;          // [N] by a run's first row: the run of its cell before it
+    int32_t *tile_sum;     // [scan_tiles(ncell)], every kTilePad words: particles of each tile of cells, zero between builds
+    int32_t *ticket;       // not read: the scan is one pass
     const int32_t *gate;   // null: always build; else build only when *gate != 0
     int rare;              // the gate is closed in most launches (lists with a skin)
 };
 __host__ __device__ inline int scan_tiles(int ncell) { return (ncell + kScanTile - 1) / kScanTile; }
 // Systems of at most kSmallBuildCells cells built by one workgroup in one launch:
 // up to kSmallBuildN particles always (rebuilt every step, us a step against the
-// five launches: N = 1000 36 and 51, 4000 44 and 53), up to kSmallBuildRareN
-// where the gate is mostly closed (N = 10 007, rebuilt every ~15 steps: 30 and
-// 37; rebuilt every step N = 8000 would take 75 us instead of 55).
+// three launches: N = 1000 30 and 37, 3000 36 and 39), up to kSmallBuildRareN
+// where the gate is mostly closed (N = 10 007, Gamma = 100: 23.5 and 31; Gamma = 10,
+// rebuilt every third step: 29 and 31; rebuilt at most steps, Gamma = 1: 35 and 32).
 constexpr int kSmallBuildCells = 16384;
 constexpr int kSmallBuildN = 4096;
 constexpr int kSmallBuildRareN = 16384;
-// ids + counts + snapshot, scan (which leaves the counts zero again), scatter,
-// stable rank + move; `count` must be zero on entry
+// ids + counts + snapshot, scan (which leaves the counts zero again), stable rank
+// + move (which leaves the tile sums zero); both must be zero on entry
 hipError_t launch_cell_build(const CellArgs &a, hipStream_t st);
 // the same for every replica of a work list: per256 has ceil(N/256) items per
 // replica, pertile scan_tiles(ncell)
