@@ -15,10 +15,10 @@ static bool vm_ok(const RhoArgs &a) { return a.vm || (a.nG >= 1 && a.nG <= kMaxG
 // Partial sums per (group, sample): rho_partial_body (shared with the near
 // kernels, which run it in some of their workgroups) is in dev_common.h.
 
-template <bool CELL, bool MIXED>
+template <bool CELL, bool MIXED, bool FINE>
 __global__ __launch_bounds__(kBlock) void k_rho_partial(RhoArgs a)
 {
-    rho_partial_body<CELL, MIXED, false>(a, (int)blockIdx.x);
+    rho_partial_body<CELL, MIXED, FINE>(a, (int)blockIdx.x);
 }
 
 // rho_reduce_body is in dev_common.h.
@@ -65,18 +65,29 @@ int rho_chunk_shared(int N, int P, bool mixed)
     return std::max(c, rho_chunk(N, P));
 }
 
+constexpr int kRhoFineBlocks = 1536;
+
 hipError_t launch_rho_partial(const RhoArgs &a, hipStream_t st)
 {
     if (!rho_partial_ok(a)) return hipErrorInvalidValue;
     const int64_t lanes = (int64_t)a.nchunk * a.P;
     dim3 grid((unsigned)((lanes + kBlock - 1) / kBlock));
-    size_t lds = rho_lds_bytes(a.P, a.chunk, a.mixed, false);
+    // The finer table takes two FMAs of 20 off each (particle, mode) term and 14 KB of
+    // LDS more, which each workgroup fills first: for launches of several workgroups
+    // per compute unit.  N = 262 147, P = 500 (2 001 workgroups): 97 -> 93 us; N = 1e6,
+    // P = 300 (4 580): 207 -> 200; N = 2e4, P = 500 (1 221): 16 and 16; N = 262 147,
+    // P = 200 in 801 workgroups: 51 -> 52.
+    const bool fine = !a.mixed && a.tab_fine && lanes >= (int64_t)kRhoFineBlocks * kBlock;
+    const size_t lds = rho_lds_bytes(a.P, a.chunk, a.mixed, fine);
+    const dim3 block(kBlock);
     if (a.xs) {
-        if (a.mixed) hipLaunchKernelGGL((k_rho_partial<true, true>), grid, dim3(kBlock), lds, st, a);
-        else hipLaunchKernelGGL((k_rho_partial<true, false>), grid, dim3(kBlock), lds, st, a);
+        if (a.mixed) hipLaunchKernelGGL((k_rho_partial<true, true, false>), grid, block, lds, st, a);
+        else if (fine) hipLaunchKernelGGL((k_rho_partial<true, false, true>), grid, block, lds, st, a);
+        else hipLaunchKernelGGL((k_rho_partial<true, false, false>), grid, block, lds, st, a);
     } else {
-        if (a.mixed) hipLaunchKernelGGL((k_rho_partial<false, true>), grid, dim3(kBlock), lds, st, a);
-        else hipLaunchKernelGGL((k_rho_partial<false, false>), grid, dim3(kBlock), lds, st, a);
+        if (a.mixed) hipLaunchKernelGGL((k_rho_partial<false, true, false>), grid, block, lds, st, a);
+        else if (fine) hipLaunchKernelGGL((k_rho_partial<false, false, true>), grid, block, lds, st, a);
+        else hipLaunchKernelGGL((k_rho_partial<false, false, false>), grid, block, lds, st, a);
     }
     return hipGetLastError();
 }

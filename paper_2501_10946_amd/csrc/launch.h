@@ -235,9 +235,10 @@ struct RhoArgs {
     int mixed;
     const double2 *tab;        // [kPhaseTab] (sin, cos)(2 pi j / kPhaseTab) (FP64 path)
     SinCosShort ss;
-    // the far field's finer table ([kFarTab] entries), used by the partial
-    // sums of a step (near launch, served ensemble): two FMA fewer per
-    // (particle, mode) than the kPhaseTab form, at 14 KB more LDS
+    // a finer table ([kFarTab] entries; null without one), used by the partial
+    // sums of a step (near launch, served ensemble) and by large launches of
+    // their own: two FMA fewer per (particle, mode) than the kPhaseTab form, at
+    // 14 KB more LDS
     const double2 *tab_fine;
     SinCosFar sf;
 };
@@ -248,7 +249,7 @@ hipError_t launch_rho_reduce(const RhoArgs &a, hipStream_t st);
 hipError_t launch_rho_full(const RhoArgs &a, hipStream_t st);
 // workgroups of the partial kernel and its dynamic LDS bytes
 __host__ __device__ inline int64_t rho_blocks(int nchunk, int P) { return ((int64_t)nchunk * P + kBlock - 1) / kBlock; }
-// (fine: the kFarTab table of a step's partial sums)
+// (fine: with the kFarTab table)
 size_t rho_lds_bytes(int P, int chunk, bool mixed, bool fine);
 // the reduction: one workgroup per kRedModes adjacent samples
 constexpr int kRedModes = 4;
