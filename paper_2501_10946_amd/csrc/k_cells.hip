@@ -29,8 +29,7 @@ __device__ inline bool gate_open(const int32_t *gate) { return gate == nullptr |
 // build of up to 1e5 particles is bound by them too.  Two more (a pass of its own
 // for the sums of the scan's tiles, a scatter of the members into their cells) took
 // 20 steps of N = 1e5 from 1437 to 1500 us, an evaluation of N = 5003 from 55 to
-// 62; at N = 1e6 the chains' atomics cost what the launches save (82 and 82 us a
-// build).
+// 62, a build of N = 1e6 from 71 to 82.
 // ---------------------------------------------------------------------------
 
 // Every kernel body takes its argument block and its workgroup index b within
@@ -102,9 +101,24 @@ __device__ inline void cell_ids_body(const CellArgs &a, int b)
         atomicAdd(&a.count[id], n);
         a.tmp[p] = (int32_t)atomicExch((uint32_t *)&a.fill[id], (uint32_t)p | ((uint32_t)(n - 1) << (32 - kRunBits)));
     }
+    // up to a thread's worth of tiles first summed in the workgroup: rows in the
+    // caller's order (a system's first build) reach every tile from every wave, and
+    // their atomics queue on the few sums (37 us a build of 4 000 to 50 000
+    // particles, 5 so; N = 1e6 in the order of an earlier build 42 and 30)
     const int tile = live ? id / kScanTile : -1;
     const int nt = run_length(tile, live);
-    if (nt > 0) atomicAdd(&a.tile_sum[tile * kTilePad], nt);
+    const int ntiles = scan_tiles(a.g.ncell);
+    if (ntiles > kBlock) {   // uniform
+        if (nt > 0) atomicAdd(&a.tile_sum[tile * kTilePad], nt);
+        return;
+    }
+    __shared__ int32_t sum[kBlock];
+    sum[threadIdx.x] = 0;
+    __syncthreads();
+    if (nt > 0) atomicAdd(&sum[tile], nt);
+    __syncthreads();
+    const int32_t v = sum[threadIdx.x];
+    if (v > 0) atomicAdd(&a.tile_sum[threadIdx.x * kTilePad], v);
 }
 
 __device__ inline int32_t block_exclusive_scan_256(int32_t v, int32_t *sh, int32_t *total)

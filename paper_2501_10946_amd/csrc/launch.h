@@ -15,7 +15,7 @@ constexpr int kBlock = 256;        // threads per workgroup of the streaming and
 constexpr int kScanPer = 8;        // cell counts per thread of the scan
 constexpr int kScanTile = kBlock * kScanPer;
 // words from one tile's sum to the next: a memory line each (with all sums in a few
-// lines the id pass of N = 1e6 takes 240 us, so 42)
+// lines the id pass of N = 1e6 took 240 us, so 42)
 constexpr int kTilePad = 32;
 constexpr int kRhoChunkMax = 256;  // particles per structure-factor group (at most)
 constexpr int kRhoStage = 1024;    // particles one structure-factor workgroup stages at most
