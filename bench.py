@@ -78,9 +78,9 @@ KERNEL_SOURCES = {
 # WRITE_SIZE 262147 KiB for 262144 KiB written: x1.000).
 MEASURED_TRAFFIC = {
     # kernel: (sources sha256, FETCH_SIZE KiB, WRITE_SIZE KiB, fetch scale, write scale)
-    "near": ("2edc4d3d5daba9c89dc3bd03b92b66876eec853fe4d09cafb3ce0c42d98c9f5a", 419413.0, 100836.0, 2.0, 1.0),
-    "far": ("8a7c054038bc2072189517df0d36b38d52c239fcc80a1550dab3e5fc888b6711", 78336.0, 78613.0, 2.0, 1.0),
-    "nlist": ("adf973cba8197b26cebf41bd16d350515c2037a2819a967fb5d13af835ff96be", 83770.0, 517545.0, 2.0, 1.0),
+    "near": ("bb9038cd7d135176c70f3c7e1c428dad90ce9f707eb5adc146345c495780f53c", 417528.0, 53961.0, 2.0, 1.0),
+    "far": ("515bcf292199a61169899e3ba4c243c53a3fa6a683cc509d8632552a01386d06", 55492.0, 78392.0, 2.0, 1.0),
+    "nlist": ("c2c5a47f54fbe811336f7995870d4bf866da6212b1bf51e0564a57d93884a61a", 83838.0, 517244.0, 2.0, 1.0),
 }
 
 # VALU issue at the same workload (FP64): VALU busy = SQ_ACTIVE_INST_VALU x 4
@@ -89,9 +89,9 @@ MEASURED_TRAFFIC = {
 # fraction of the VALU's lane-cycles that issued work.
 MEASURED_VALU = {
     # kernel: (sources sha256, VALU busy, lane utilisation)
-    "near": ("2edc4d3d5daba9c89dc3bd03b92b66876eec853fe4d09cafb3ce0c42d98c9f5a", 0.79, 0.89),
-    "far": ("8a7c054038bc2072189517df0d36b38d52c239fcc80a1550dab3e5fc888b6711", 0.89, 1.00),
-    "nlist": ("adf973cba8197b26cebf41bd16d350515c2037a2819a967fb5d13af835ff96be", 0.83, 0.76),
+    "near": ("bb9038cd7d135176c70f3c7e1c428dad90ce9f707eb5adc146345c495780f53c", 0.79, 0.97),
+    "far": ("515bcf292199a61169899e3ba4c243c53a3fa6a683cc509d8632552a01386d06", 0.91, 1.00),
+    "nlist": ("c2c5a47f54fbe811336f7995870d4bf866da6212b1bf51e0564a57d93884a61a", 0.76, 0.75),
 }
 
 

@@ -90,7 +90,7 @@ void box_edges(const rbsog_params *p, double Lb[3]);
 // the host's libm: the rotation table of the FP64 phase kernels (2 * kPhaseTable words)
 constexpr int kPhaseTable = 128;
 const double *phase_table();
-// the far field's finer table, (sin, cos)(2 pi j / 1024)
+// the finer table of a step's structure-factor partials, (sin, cos)(2 pi j / 1024)
 constexpr int kFarTable = 1024;
 const double *far_table();
 // sum q and sum q^2 in particle order (plain FP64 additions, no contraction)
