@@ -78,9 +78,9 @@ KERNEL_SOURCES = {
 # WRITE_SIZE 262147 KiB for 262144 KiB written: x1.000).
 MEASURED_TRAFFIC = {
     # kernel: (sources sha256, FETCH_SIZE KiB, WRITE_SIZE KiB, fetch scale, write scale)
-    "near": ("bb9038cd7d135176c70f3c7e1c428dad90ce9f707eb5adc146345c495780f53c", 417528.0, 53961.0, 2.0, 1.0),
-    "far": ("515bcf292199a61169899e3ba4c243c53a3fa6a683cc509d8632552a01386d06", 55492.0, 78392.0, 2.0, 1.0),
-    "nlist": ("c2c5a47f54fbe811336f7995870d4bf866da6212b1bf51e0564a57d93884a61a", 83838.0, 517244.0, 2.0, 1.0),
+    "near": ("bc4d6e53a0cfa472b8adb77c2f111b2f82bc2225ffd6e094f8653ae4802d0387", 417528.0, 53961.0, 2.0, 1.0),
+    "far": ("bf2f60c322b81bd10ede99699c6392fb364ae7ea6ef296dc67de0602e1996c82", 55492.0, 78392.0, 2.0, 1.0),
+    "nlist": ("65c2fe290e18411a1516ad105766501f64b9441aa9cfa2b1d5b7f05d28c0dcf7", 83838.0, 517244.0, 2.0, 1.0),
 }
 
 # VALU issue at the same workload (FP64): VALU busy = SQ_ACTIVE_INST_VALU x 4
@@ -89,9 +89,9 @@ MEASURED_TRAFFIC = {
 # fraction of the VALU's lane-cycles that issued work.
 MEASURED_VALU = {
     # kernel: (sources sha256, VALU busy, lane utilisation)
-    "near": ("bb9038cd7d135176c70f3c7e1c428dad90ce9f707eb5adc146345c495780f53c", 0.79, 0.97),
-    "far": ("515bcf292199a61169899e3ba4c243c53a3fa6a683cc509d8632552a01386d06", 0.91, 1.00),
-    "nlist": ("c2c5a47f54fbe811336f7995870d4bf866da6212b1bf51e0564a57d93884a61a", 0.76, 0.75),
+    "near": ("bc4d6e53a0cfa472b8adb77c2f111b2f82bc2225ffd6e094f8653ae4802d0387", 0.79, 0.97),
+    "far": ("bf2f60c322b81bd10ede99699c6392fb364ae7ea6ef296dc67de0602e1996c82", 0.91, 1.00),
+    "nlist": ("65c2fe290e18411a1516ad105766501f64b9441aa9cfa2b1d5b7f05d28c0dcf7", 0.76, 0.75),
 }
 
 

@@ -503,14 +503,9 @@ int evaluate(rbsog_handle *h, const double4 *samp, double *f, double *f_near, bo
         // the partial sums run in the near kernel's first workgroups
         na.red = ra;
         na.nrho = (int)((rho_blocks(ra.nchunk, ra.P) + 7) / 8 * 8);
-        // Spread through a launch of several rounds of workgroups, the partial
-        // sums fill the issue slots the near field's gathers leave (N = 3e5,
-        // 7 032 workgroups: 600 -> 598 us an evaluation; the evaluation with three
-        // lanes per particle gained far more: N = 1e6, 0.91 -> 0.74 ms).  A launch
-        // the chip holds at once runs best with the longer partial-sum
-        // workgroups dispatched first (N = 1e5, 2 176 workgroups: a step 83 us
-        // first, 88 us spread).
-        na.interleave = (int64_t)na.nrho + near_blocks((int)h->p.N) >= kInterleaveBlocks;
+        // spread through the launch they fill the issue slots the near field's
+        // gathers leave; first, their longer workgroups start early
+        na.interleave = near_spread(na.mixed, na.nrho, near_blocks((int)h->p.N));
         if (const char *e = std::getenv("RBSOG_NEAR_INTERLEAVE"))   // 0 / 1: a tuning knob
             na.interleave = std::atoi(e) != 0;
     }

@@ -274,15 +274,14 @@ int rebuild_lists(rbsog_ens *s)
     // the draws run beside the drift
     L[rbsog_ens::LKICK].insert(L[rbsog_ens::LKICK].end(), L[rbsog_ens::L256].begin(), L[rbsog_ens::L256].end());
     // the partial sums run beside the near field of their precision, as in a
-    // system's own launch: before it when the chip holds them all at once, else
-    // spread evenly through it
+    // system's own launch: before it, or spread evenly through it (near_spread)
     for (int pr = 0; pr < 2; ++pr) {
         std::vector<EnsItem> &near = L[pr ? rbsog_ens::LNEARMIXED
                                           : L[rbsog_ens::LNEARPOLY].empty() ? rbsog_ens::LNEAREXP : rbsog_ens::LNEARPOLY];
         const size_t nr = rho[pr].size(), nn = near.size();
         std::vector<EnsItem> both;
         both.reserve(nr + nn);
-        if ((int64_t)(nr + nn) < kInterleaveBlocks) {
+        if (!near_spread(pr == 1, (int64_t)nr, (int64_t)nn)) {
             both = rho[pr];
             both.insert(both.end(), near.begin(), near.end());
         } else {

@@ -288,9 +288,19 @@ struct NearArgs {
     int interleave;
     RhoArgs red;
 };
-// near launches of at least this many workgroups (several rounds of the chip's
-// resident workgroups) spread their structure-factor workgroups (interleave)
-constexpr int64_t kInterleaveBlocks = 3072;
+// Whether a near launch spreads its nrho structure-factor workgroups among its
+// near workgroups (interleave) or runs them first: in FP64 where they are several
+// rounds of the chip by themselves (5 steps of r_c = 5, P = 500, us first and
+// spread: N = 2e5, 1528 workgroups of them, 1600 and 1649; 2.5e5, 1909: 1955 and
+// 1989; 4e5, 3053: 3245 and 3112; 1e6: 7795 and 7405; 20 of r_c = 4, P = 200: N = 1.4e5,
+// 1710: 1968 and 2055; 5e5, 1526: 6060 and 6198), in mixed precision, whose sums are
+// shorter, where the whole launch is (N = 6e4, 1854 workgroups in all: 407 and 409; 1e5,
+// 3090: 603 and 600; 2e5: 1056 and 1028; 1e6: 5400 and 4904).
+constexpr int64_t kSpreadRho = 2176, kSpreadAll = 3072;
+inline bool near_spread(bool mixed, int64_t nrho, int64_t nnear)
+{
+    return mixed ? nrho + nnear >= kSpreadAll : nrho >= kSpreadRho;
+}
 hipError_t launch_nlist(const NearArgs &a, hipStream_t st);
 // workgroups per system: list build (cell pairs of the fine grid of nf cells per axis), evaluation
 // (kNearHomes particles), far field (64 particles)
