@@ -391,6 +391,10 @@ extern "C" int rbsog_ssf(int64_t N, double L, const double *x_dev, const double 
         a.N = (int)N;
         a.P = (int)std::min<int64_t>(pl.pass, pl.K - c0);
         a.chunk = pl.pass == pl.P ? rho_chunk((int)N, a.P) : pl.chunk;
+        // a short last pass: a workgroup of few modes stages more groups, so smaller
+        // ones (the partials fit: below 86 modes of groups that fill the staging area,
+        // under N + P of them, where a full pass has 4 N)
+        while ((255 / a.P + 2) * a.chunk > kRhoStage) a.chunk /= 2;
         a.nchunk = (int)((N + a.chunk - 1) / a.chunk);
         a.inv_L[0] = a.inv_L[1] = a.inv_L[2] = 1.0 / L;
         a.x = x_dev;
