@@ -756,7 +756,8 @@ int create_system(const rbsog_params *p, const rbsog_sog *s, const double *q_dev
     if (e == hipSuccess)   // a cell order before the first build
         e = up ? up->fill(h->order, sizeof(int32_t) * (size_t)p->N, kCopyIota) : launch_iota(h->order, (int)p->N, h->st);
     // the uploads above are from host memory this function releases
-    if (e == hipSuccess && !up) e = hipStreamSynchronize(h->st);
+    const hipError_t us = up ? up->settle() : hipStreamSynchronize(h->st);
+    if (e == hipSuccess) e = us;
     if (e != hipSuccess) {
         delete h;
         return fail(RBSOG_EHIP, "uploading tables: %s", hipGetErrorString(e));

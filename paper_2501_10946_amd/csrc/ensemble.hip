@@ -71,9 +71,15 @@ hipError_t Uploads::flush()
     hipError_t e = segs.n > 0 ? launch_copy_segs(segs, st) : hipSuccess;
     segs.n = 0;
     if (e == hipSuccess) e = hipEventRecord(done, st);
-    if (e == hipSuccess && direct) e = hipStreamSynchronize(st);   // the caller's arrays are still being read
+    const hipError_t es = settle();
+    return e == hipSuccess ? es : e;
+}
+
+hipError_t Uploads::settle()
+{
+    if (!direct) return hipSuccess;
     direct = false;
-    return e;
+    return hipStreamSynchronize(st);
 }
 
 namespace {

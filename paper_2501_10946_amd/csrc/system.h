@@ -184,21 +184,23 @@ bool adapt_skin(rbsog_handle *h, double dt);
 bool adapt_skin_rebuilds(rbsog_handle *h);
 // Host arrays on their way to the device: copied into pinned memory, from where
 // one kernel per flush (on the stream st) moves all of them, with the fills that
-// go along.  What does not fit goes by hipMemcpyAsync from where it lies, and the
-// flush then waits for the stream.  The pinned memory may be filled again (reset)
-// once the kernel of the last flush is done.
+// go along.  What does not fit goes by hipMemcpyAsync from where it lies: its owner
+// settles the uploads before that memory changes or goes (a flush settles them too).
+// The pinned memory may be filled again (reset) once the kernel of the last flush is
+// done.
 struct Uploads {
     hipStream_t st = nullptr;
     hipEvent_t done = nullptr;   // recorded by each flush
     char *host = nullptr;        // pinned, read by the device at this address
     size_t cap = 0, used = 0;
     CopySegs segs{};
-    bool direct = false;
+    bool direct = false;         // a copy from where its source lies may be on its way
     // waits until the device has read what the last flush sent, then starts again
     hipError_t reset();
     hipError_t copy(void *dst, const void *src, size_t bytes);
     hipError_t fill(void *dst, size_t bytes, int32_t kind);   // kCopyZero or kCopyIota
     hipError_t flush();
+    hipError_t settle();         // waits for the copies from where their sources lie
 };
 // rbsog_create; with lattice_dev (the packed lattice up to at least the
 // system's m_max, owned by the caller) the workspace holds no lattice copy

@@ -45,6 +45,7 @@ inline std::vector<Copy> pending;                         // copies from the hos
 inline std::function<void(const Launch &)> on_launch;
 inline int fail_launch = -1;                              // the launch (counted from 0) that fails, once
 inline int launches = 0, stale = 0;
+inline std::map<hipStream_t, bool> busy;                  // streams with launches nothing has waited for
 inline hipError_t last_error = hipSuccess;
 struct Config {
     dim3 grid, block;
@@ -53,8 +54,17 @@ struct Config {
 };
 inline std::vector<Config> configs;
 
+inline bool waited_for_all()
+{
+    for (const auto &b : busy)
+        if (b.second) return false;
+    return pending.empty();
+}
+
 inline void carry_out(bool all, hipStream_t st)
 {
+    if (all) busy.clear();
+    else busy[st] = false;
     std::vector<Copy> rest;
     for (Copy &c : pending) {
         if (!all && c.stream != st) {
@@ -104,6 +114,7 @@ hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, s
 {
     if (host_runtime::launches++ == host_runtime::fail_launch)
         return host_runtime::last_error = hipErrorLaunchFailure;
+    host_runtime::busy[st] = true;
     if (host_runtime::on_launch) host_runtime::on_launch({host_runtime::kernels()[fn], grid, block, lds, st, args[0]});
     return hipSuccess;
 }
