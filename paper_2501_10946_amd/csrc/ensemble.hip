@@ -446,6 +446,17 @@ void drop_replica(rbsog_ens *s, int r)
     R = Replica{};
 }
 
+// A failed admission: its range of the pool and its arrays are free again once nothing
+// that it has sent or launched is still under way (launched: on st too).
+void abandon_admission(rbsog_ens *s, int slot, bool launched)
+{
+    s->up.segs.n = 0;
+    s->up.direct = false;
+    (void)hipStreamSynchronize(s->up.st);
+    if (launched) (void)hipStreamSynchronize(s->st);
+    drop_replica(s, slot);
+}
+
 }  // namespace
 
 extern "C" int rbsog_ens_create(size_t hbm_budget, int max_slots, void *hip_stream, rbsog_ens **out)
@@ -568,7 +579,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
     if (e == hipSuccess) e = s->up.copy(R.q, q_host, sizeof(double) * N);
     if (e == hipSuccess) e = s->up.copy(R.m, m_host, sizeof(double) * N);
     if (e != hipSuccess) {
-        drop_replica(s, slot);
+        abandon_admission(s, slot, false);
         return ens_fail_hip(e, "uploading the replica");
     }
     rc = create_system(p, sog, R.q, R.m, wsp, align_up(ws), s->up.st, s->lat, &R.h, &d, q_host, m_host, &s->up);
@@ -578,7 +589,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
         if (e != hipSuccess) rc = ens_fail_hip(e, "uploading the replica");
     }
     if (rc) {
-        drop_replica(s, slot);
+        abandon_admission(s, slot, false);
         return rc;
     }
     R.h->st = s->st;
@@ -591,7 +602,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
         if (le != hipSuccess) rc = ens_fail_hip(le, "moving the replica into cell order");
     }
     if (rc) {
-        drop_replica(s, slot);
+        abandon_admission(s, slot, true);
         return rc;
     }
     // the default skin meets the time step here, as at a system's first
@@ -600,7 +611,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
     if (adapt_skin(R.h, dt)) {
         hipError_t le = launch_set_int(R.h->gate, 1, s->st);
         if (le != hipSuccess) {
-            drop_replica(s, slot);
+            abandon_admission(s, slot, true);
             return ens_fail_hip(le, "raising the replica's rebuild gate");
         }
     }
@@ -609,7 +620,7 @@ extern "C" int rbsog_ens_admit(rbsog_ens *s, const rbsog_params *p, const rbsog_
     R.e_adm = s->E;
     rc = write_tables(s, slot, dt);
     if (rc) {
-        drop_replica(s, slot);
+        abandon_admission(s, slot, true);
         return rc;
     }
     R.active = true;

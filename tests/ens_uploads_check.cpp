@@ -1,7 +1,7 @@
 // Admissions and the memory their uploads read from: what goes up has arrived when
 // its source is changed or released, whether it fits the pinned memory or not, and
-// nothing of the caller's is still being read when an admission returns.  Arguments:
-// particle counts.
+// nothing of the caller's is still being read when an admission returns, be it refused,
+// failed or carried out.  Arguments: particle counts.
 #include "host_runtime.h"
 #include "system.h"
 
@@ -49,8 +49,8 @@ static void admissions(int64_t N)
         std::exit(2);
     rbsog_ens *ens = nullptr;
     if (rbsog_ens_create(3 * bytes, 3, nullptr, &ens) != RBSOG_OK) std::exit(2);
-    std::vector<double> x(3 * N, 1.0), v(3 * N, 0.5), q(N, 1.0), m(N, 1.0);
-    const std::vector<double> *mine[] = {&x, &v, &q, &m};
+    std::vector<double> x(3 * N, 1.0), v(3 * N, 0.5), q(N, 1.0), m(N, 1.0), zero(N, 0.0);
+    const std::vector<double> *mine[] = {&x, &v, &q, &m, &zero};
     auto free_again = [&](const char *what) {
         for (const std::vector<double> *a : mine) expect(!reads(a->data(), 8 * a->size()), N, what);
     };
@@ -63,6 +63,24 @@ static void admissions(int64_t N)
     }
     host_runtime::carry_out(true, nullptr);
     expect(host_runtime::stale == 0, N, "a source changed before its copy was waited for");
+    settle();
+    // refused after its state has been sent
+    expect(rbsog_ens_admit(ens, &p, &sog, x.data(), v.data(), zero.data(), m.data(), 4, 0.01, &slot) == RBSOG_EINVAL,
+           N, "charges of zero are refused");
+    free_again("a refused admission returns while its arrays are read");
+    settle();
+    // a launch that fails, at each of the admission's launches in turn
+    for (int at = 0; at < 12; ++at) {
+        host_runtime::launches = 0;
+        host_runtime::fail_launch = at;
+        const int rc = rbsog_ens_admit(ens, &p, &sog, x.data(), v.data(), q.data(), m.data(), 4, 0.01, &slot);
+        host_runtime::fail_launch = -1;
+        if (rc == RBSOG_OK) break;   // fewer launches than that
+        expect(rc == RBSOG_EHIP, N, "a failed launch is reported");
+        expect(host_runtime::waited_for_all(), N, "a failed admission returns its pool range with work in flight");
+        free_again("a failed admission returns while its arrays are read");
+        settle();
+    }
     rbsog_ens_destroy(ens);
     settle();
 }
