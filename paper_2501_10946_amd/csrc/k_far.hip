@@ -113,6 +113,8 @@ __device__ inline void far_body(const FarArgs &a, int b)
         s[i][0] = pi.x * a.inv_L[0];
         s[i][1] = pi.y * a.inv_L[1];
         s[i][2] = pi.z * a.inv_L[2];
+        if (!MIXED)   // whole revolutions off, exactly: half the phase's rounding
+            for (int d = 0; d < 3; ++d) s[i][d] -= rint(s[i][d]);
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c][i][0] = acc[c][i][1] = acc[c][i][2] = 0.0;
     }

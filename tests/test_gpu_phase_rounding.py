@@ -1,0 +1,54 @@
+"""Rounding of the far field's phases against extended precision (FP64): the force's
+error stays below that of the form that rotates a table entry by each phase and
+multiplies by rho, which was measured on these inputs (RMS error over RMS force)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+import paper_2501_10946_amd as R  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+LD = np.longdouble
+PI = LD("3.14159265358979323846264338327950288")
+
+
+def modes(h, step, P):
+    n = torch.zeros((P, 3), dtype=torch.int32, device="cuda")
+    coef = torch.zeros(P, dtype=torch.float64, device="cuda")
+    R.rbsog_sample_k(h, step, n, coef)
+    torch.cuda.synchronize()
+    return n.cpu().numpy(), coef.cpu().numpy()
+
+
+# eight particles around the sites of a lattice with no pair within the cutoff, so that
+# the force is the far field alone; two charges; the table form's error
+@pytest.mark.parametrize("kappa, edge, table_form", [(1.0, 3.01, 2.0348e-15), (0.5, 3.01, 2.2498e-15),
+                                                     (0.5, 6.0, 3.1840e-15), (1.0, 12.0, 4.7701e-15)])
+def test_far_force(orc, kappa, edge, table_form):
+    r_c, N, P, evaluations = (2.0 if edge == 12.0 else 3.0), 8, 20, 400
+    L = r_c * edge
+    o = orc.sog_auto(1 / kappa, r_c, 1e-4)
+    q = np.array([1.0, 2.0] * 4)
+    s = R.System(q, np.ones(N), L, R.sog_from_parameters(o.lam, o.rc, o.h, o.t0, o.w, o.M1, o.M2), 1.0, P, seed=5,
+                 device=torch.device("cuda"))
+    rng = np.random.default_rng(11)
+    site = np.stack(np.meshgrid([0.25, 0.75], [0.25, 0.75], [0.25, 0.75], indexing="ij")).reshape(3, 8)
+    err = size = 0.0
+    for step in range(evaluations):
+        shift = rng.random((3, 1))
+        x = np.mod(site + shift + 0.07 * (rng.random((3, N)) - 0.5), 1.0) * L
+        x[x >= L] = 0
+        xd = torch.tensor(x, device="cuda")
+        f, f_near = torch.empty_like(xd), torch.empty_like(xd)
+        R.rbsog_compute_forces(s.h, step, xd, f, f_near, None)
+        n, coef = modes(s.h, step, P)
+        assert float(f_near.abs().max()) == 0.0
+        u = n.astype(LD) @ (x.astype(LD) / LD(L))
+        th = 2 * PI * (u - np.rint(u))
+        c, d = np.cos(th), np.sin(th)
+        im = c * (q * d).sum(1)[:, None] - d * (q * c).sum(1)[:, None]
+        exact = -(2 * PI / LD(L)) * q * ((coef.astype(LD)[:, None] * im).T @ n.astype(LD)).T
+        err += float(((f.cpu().numpy() - exact) ** 2).sum())
+        size += float((exact ** 2).sum())
+    assert (err / size) ** 0.5 <= table_form
