@@ -165,17 +165,23 @@ __device__ inline void kick_drift_body(const KickDriftArgs &a, int b)
 // kernel adds the partials of each sample in a fixed order.
 // ---------------------------------------------------------------------------
 
-// One particle's term q exp(i k.r) of a mode; p holds (r/L, q) (mixed) or
-// (T r/L, q) (FP64, T the entries of the rotation table: kPhaseTab, or
-// kFarTab with FINE), so that k.p is the phase in the unit that the
-// precision's sine and cosine take.  UNIT (FP64): exp(i k.r) alone, the rotation
+// x inv_L less whole revolutions, in one rounding: n times it is the phase less whole
+// revolutions, with half the rounding of n (x inv_L) and of the sums over the axes.
+__device__ inline double less_turns(double x, double inv_L) { return fma(x, inv_L, -rint(x * inv_L)); }
+
+// One particle's term q exp(i k.r) of a mode; k.p is the phase in the unit that the
+// precision's sine and cosine take: revolutions (mixed) or 1/T of them (FP64, T the
+// entries of the rotation table: kPhaseTab, or kFarTab with FINE).  UNIT (FP64): exp(i k.r) alone, the rotation
 // by the table entry accumulated as it is formed (the caller multiplies the sum
-// by the charge all its particles have): two instructions fewer of 20.  Bound by
-// those instructions; with the loop of rho_group 262 147 particles and 500 modes
-// take 104 us where one loop over charges and pairs of particles took 118.
+// by the charge all its particles have): two instructions fewer of 20.  Its large
+// parts go to re, im and its small ones (with the rotation's sine, at most pi/T) to
+// re1, im1, re - re1 and im + im1 being the term: one rounding a term at the size of
+// the sum, as where the rotated values are formed first, not two.  Bound by its
+// instructions: 262 147 particles and 500 modes take 93 us, where the loop over charges
+// and pairs of particles took 105.
 template <bool MIXED, bool FINE = false, bool UNIT = false>
 __device__ inline void rho_term(const RhoArgs &a, const double2 *tab, const double4 &k, const double4 &p,
-                                double &re, double &im)
+                                double &re, double &im, double *re1 = nullptr, double *im1 = nullptr)
 {
     static_assert(!(MIXED && UNIT), "the mixed terms take the charge");
     double u = k.x * p.x + k.y * p.y + k.z * p.z;
@@ -191,8 +197,8 @@ __device__ inline void rho_term(const RhoArgs &a, const double2 *tab, const doub
         else rotation_tab(u, tab, a.ss, &t, &sp, &cp);
         re = fma(t.y, cp, re);
         im = fma(t.x, cp, im);
-        re = fma(-t.x, sp, re);
-        im = fma(t.y, sp, im);
+        *re1 = fma(t.x, sp, *re1);
+        *im1 = fma(t.y, sp, *im1);
     } else {
         double sn, cs;
         if (FINE) sincos_rev_far(u, tab, a.sf, &sn, &cs);
@@ -208,16 +214,16 @@ __device__ inline void rho_term(const RhoArgs &a, const double2 *tab, const doub
 template <bool MIXED, bool FINE, bool UNIT>
 __device__ inline double2 rho_group(const RhoArgs &a, const double2 *tab, const double4 &k, const double4 *sp, int n)
 {
-    double re0 = 0.0, im0 = 0.0, re1 = 0.0, im1 = 0.0;
+    double re0 = 0.0, im0 = 0.0, re1 = 0.0, im1 = 0.0, rs = 0.0, is = 0.0;
     int i = 0;
     for (; i + 3 < n; i += 4) {
-        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i], re0, im0);
-        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 1], re1, im1);
-        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 2], re0, im0);
-        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 3], re1, im1);
+        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i], re0, im0, &rs, &is);
+        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 1], re1, im1, &rs, &is);
+        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 2], re0, im0, &rs, &is);
+        rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i + 3], re1, im1, &rs, &is);
     }
-    for (; i < n; ++i) rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i], re0, im0);
-    return make_double2(re0 + re1, im0 + im1);
+    for (; i < n; ++i) rho_term<MIXED, FINE, UNIT>(a, tab, k, sp[i], re0, im0, &rs, &is);
+    return UNIT ? make_double2(re0 + re1 - rs, im0 + im1 + is) : make_double2(re0 + re1, im0 + im1);
 }
 
 template <bool CELL, bool MIXED, bool FINE>
@@ -234,10 +240,6 @@ __device__ inline void rho_partial_body(const RhoArgs &a, int b)
     const int s_hi = (int)min((int64_t)a.nchunk - 1, (g0 + kBlock - 1) / a.P);
     const int j_lo = s_lo * a.chunk;
     const int j_hi = min(a.N, (s_hi + 1) * a.chunk);
-    // phase units of the precision, per axis
-    const double phx = MIXED ? a.inv_L[0] : a.inv_L[0] * T;
-    const double phy = MIXED ? a.inv_L[1] : a.inv_L[1] * T;
-    const double phz = MIXED ? a.inv_L[2] : a.inv_L[2] * T;
     // every particle of the workgroup with one charge (a one-component plasma):
     // the sums run without it
     const double q0 = CELL ? a.xs[j_lo].w : a.q[j_lo];
@@ -248,11 +250,11 @@ __device__ inline void rho_partial_body(const RhoArgs &a, int b)
         if (CELL) v = a.xs[j];
         else v = make_double4(a.x[j], a.x[a.N + j], a.x[2 * a.N + j], a.q[j]);
         other |= !(v.w == q0);
-        double x = v.x * phx, y = v.y * phy, z = v.z * phz;
-        if (!MIXED) {   // whole revolutions off, exactly: half the phase's rounding
-            x -= T * rint(x * (1.0 / T));
-            y -= T * rint(y * (1.0 / T));
-            z -= T * rint(z * (1.0 / T));
+        double x = v.x * a.inv_L[0], y = v.y * a.inv_L[1], z = v.z * a.inv_L[2];
+        if (!MIXED) {
+            x = less_turns(v.x, a.inv_L[0]);
+            y = less_turns(v.y, a.inv_L[1]);
+            z = less_turns(v.z, a.inv_L[2]);
         }
         sp[k] = make_double4(x, y, z, v.w);
     }
@@ -264,7 +266,12 @@ __device__ inline void rho_partial_body(const RhoArgs &a, int b)
     const int64_t g = g0 + t;
     if (g >= (int64_t)a.nchunk * a.P) return;
     const int s = (int)(g / a.P), l = (int)(g - (int64_t)s * a.P);
-    const double4 k = a.samp[l];
+    double4 k = a.samp[l];
+    if (!MIXED) {   // the phase in the table's steps
+        k.x *= T;
+        k.y *= T;
+        k.z *= T;
+    }
     const double4 *group = sp + (s * a.chunk - j_lo);
     // whole groups but in the workgroup that holds the last one
     const int n = (s_hi + 1) * a.chunk <= a.N ? a.chunk : min(a.N, (s + 1) * a.chunk) - s * a.chunk;

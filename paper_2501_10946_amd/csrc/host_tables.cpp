@@ -298,14 +298,15 @@ void build_tables(const rbsog_sog &s, const rbsog_params &p, double Q2, int mmax
     for (int i = 0; i < t->nshell; ++i) t->coef.push_back(t->S / ((double)p.P * V * Fk_of[i]));
 }
 
-// (sin, cos)(2 pi j / n), j < n: 2 pi j / n is within an ulp of the exact
-// angle; the quarter turns are set exactly so that they carry no rounding
+// (sin, cos)(2 pi j / n), j < n, to the nearest FP64 value: from 2 pi j / n in the 64
+// bits of long double (an FP64 angle is up to an ulp of 2 pi off, and the entries with
+// it by 2e-16, the size of the other errors of a structure-factor term)
 static void rotation_table(double *out, int n)
 {
-    const double two_pi = 6.283185307179586;
+    const long double two_pi = 6.283185307179586476925286766559L;
     for (int j = 0; j < n; ++j) {
-        double a = two_pi * (double)j / (double)n;
-        double s = std::sin(a), c = std::cos(a);
+        const long double a = two_pi * j / n;
+        double s = (double)sinl(a), c = (double)cosl(a);
         if (j == n / 4) { s = 1.0; c = 0.0; }
         if (j == n / 2) { s = 0.0; c = -1.0; }
         if (j == 3 * n / 4) { s = -1.0; c = 0.0; }

@@ -86,8 +86,8 @@ double box_k2(const double Lb[3], int nx, int ny, int nz);
 int64_t box_lattice_points(const rbsog_sog &s, const double Lb[3]);
 // the box edges of the parameters (Ly, Lz of 0 take L)
 void box_edges(const rbsog_params *p, double Lb[3]);
-// (sin, cos)(2 pi j / kPhaseTable), j = 0 .. kPhaseTable - 1, interleaved, from
-// the host's libm: the rotation table of the FP64 phase kernels (2 * kPhaseTable words)
+// (sin, cos)(2 pi j / kPhaseTable), j = 0 .. kPhaseTable - 1, interleaved, each to
+// the nearest: the rotation table of the FP64 phase kernels (2 * kPhaseTable words)
 constexpr int kPhaseTable = 128;
 const double *phase_table();
 // the finer table of a step's structure-factor partials, (sin, cos)(2 pi j / 1024)

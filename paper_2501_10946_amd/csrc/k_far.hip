@@ -43,8 +43,8 @@ struct FarTile {
     double wz[kFarTile];
 };
 
-// Adds one mode to a particle's sum; (sx, sy, sz) is r/L, so that n.s is the
-// phase in revolutions.
+// Adds one mode to a particle's sum; s is r/L (FP64: less whole revolutions), so that
+// n.s is the phase in revolutions.
 template <bool MIXED>
 __device__ inline void far_add(const FarArgs &a, const double4 &k, const double2 &w, double wz, const double s[3],
                                double acc[3])
@@ -110,11 +110,15 @@ __device__ inline void far_body(const FarArgs &a, int b)
     for (int i = 0; i < PPL; ++i) {
         const int p = (b * PPL + i) * 64 + lane;
         const double4 pi = p < a.N ? a.xs[p] : make_double4(0.0, 0.0, 0.0, 0.0);
-        s[i][0] = pi.x * a.inv_L[0];
-        s[i][1] = pi.y * a.inv_L[1];
-        s[i][2] = pi.z * a.inv_L[2];
-        if (!MIXED)   // whole revolutions off, exactly: half the phase's rounding
-            for (int d = 0; d < 3; ++d) s[i][d] -= rint(s[i][d]);
+        if (MIXED) {
+            s[i][0] = pi.x * a.inv_L[0];
+            s[i][1] = pi.y * a.inv_L[1];
+            s[i][2] = pi.z * a.inv_L[2];
+        } else {
+            s[i][0] = less_turns(pi.x, a.inv_L[0]);
+            s[i][1] = less_turns(pi.y, a.inv_L[1]);
+            s[i][2] = less_turns(pi.z, a.inv_L[2]);
+        }
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c][i][0] = acc[c][i][1] = acc[c][i][2] = 0.0;
     }

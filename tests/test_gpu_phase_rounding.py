@@ -1,6 +1,7 @@
-"""Rounding of the far field's phases against extended precision (FP64): the force's
-error stays below that of the form that rotates a table entry by each phase and
-multiplies by rho, which was measured on these inputs (RMS error over RMS force)."""
+"""Rounding of the far field and of the structure factors against extended precision
+(FP64): the errors stay below those of the forms that rotate a table entry by each phase,
+then multiply by rho or by the charge, which were measured on these inputs (RMS error
+over RMS value)."""
 import numpy as np
 import pytest
 
@@ -50,5 +51,33 @@ def test_far_force(orc, kappa, edge, table_form):
         im = c * (q * d).sum(1)[:, None] - d * (q * c).sum(1)[:, None]
         exact = -(2 * PI / LD(L)) * q * ((coef.astype(LD)[:, None] * im).T @ n.astype(LD)).T
         err += float(((f.cpu().numpy() - exact) ** 2).sum())
+        size += float((exact ** 2).sum())
+    assert (err / size) ** 0.5 <= table_form
+
+
+# equal charges in blobs of 256 consecutive particles (as cells hold them), long waves,
+# an edge that is a power of two: what is left is the rounding of the terms and of their
+# sums
+def test_structure_factors_of_equal_charges(orc):
+    N, P, L, table_form = 65536, 500, 16.0, 6.2498e-16
+    o = orc.sog_auto(2.0, 4.0, 1e-4)
+    q = np.ones(N)
+    s = R.System(q, q, L, R.sog_from_parameters(o.lam, o.rc, o.h, o.t0, o.w, o.M1, o.M2), 1.0, P, seed=3,
+                 device=torch.device("cuda"))
+    rng = np.random.default_rng(7)
+    err = size = 0.0
+    for step in range(40):
+        centre = np.repeat(rng.random((3, N // 256)), 256, axis=1)
+        x = np.mod(centre + 0.1 * rng.random((3, N)), 1.0) * L
+        x[x >= L] = 0
+        rho = torch.zeros((P, 2), dtype=torch.float64, device="cuda")
+        R.rbsog_compute_rho(s.h, step, torch.tensor(x, device="cuda"), rho)
+        n, _ = modes(s.h, step, P)
+        _, at = np.unique(n, axis=0, return_index=True)
+        at = at[(n[at] ** 2).sum(1) <= 2]
+        u = n[at].astype(LD) @ (x.astype(LD) / LD(L))
+        th = 2 * PI * (u - np.rint(u))
+        exact = np.stack([np.cos(th).sum(1), np.sin(th).sum(1)], 1)
+        err += float(((rho.cpu().numpy()[at] - exact) ** 2).sum())
         size += float((exact ** 2).sum())
     assert (err / size) ** 0.5 <= table_form
