@@ -272,7 +272,7 @@ CellArgs cell_args(rbsog_handle *h, const CellGeom &g, const int32_t *gate, bool
     a.tile_sum = h->tile_sum;
     a.ticket = h->ticket;
     a.gate = gate;
-    a.rare = gate && h->d.skin > 0.0;
+    a.rare = gate && h->gate_rare && h->d.skin > 0.0;
     return a;
 }
 
@@ -923,6 +923,21 @@ bool adapt_skin(rbsog_handle *h, double dt)
     return true;
 }
 
+// How often the gate has been open decides how middle-sized systems build their cells
+// (the order is the same either way): looked at after kLookSteps steps or more, from a
+// count that has arrived on the host.  A system that has not been looked at, or whose
+// rebuilds are not counted (an explicit skin), counts as often rebuilt.
+constexpr int kLookSteps = 16;
+
+static void look_at_gate(rbsog_handle *h)
+{
+    const int64_t steps = h->rb_steps - h->look_steps, rebuilds = (int64_t)*h->rb_host - h->look_rebuilds;
+    if (steps < kLookSteps) return;
+    h->gate_rare = rebuilds * h->p.N <= steps * kRareRows;
+    h->look_steps += steps;
+    h->look_rebuilds += rebuilds;
+}
+
 // The thermal estimate misses systems that run hotter than their kT (a
 // random start relaxing into a strongly coupled state heats far above it):
 // there the count of rebuilt steps decides.  After each rbsog_step the device
@@ -934,6 +949,7 @@ bool adapt_skin_rebuilds(rbsog_handle *h)
     if (!h->rb_pending || !h->skin_default || h->d.skin == 0.0) return false;
     if (hipEventQuery(h->rb_ev) != hipSuccess) return false;   // not arrived yet (or an error: keep the skin)
     h->rb_pending = false;
+    look_at_gate(h);
     if (h->rb_steps < 10 || 2 * (int64_t)*h->rb_host <= h->rb_steps) return false;
     drop_skin(h);
     return true;
@@ -1033,6 +1049,9 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
     HIPCHECK(timed(h, kKickDrift, [&] { return launch_state_out(io, h->st); }));
     h->steps_done += nsteps;
     if (h->rb_host && h->skin_default && h->d.skin > 0.0) {
+        // the count of the call before, if it came too late for this one's start: calls
+        // that follow one another at once would never see one
+        if (h->rb_pending && hipEventQuery(h->rb_ev) == hipSuccess) look_at_gate(h);
         HIPCHECK(hipMemcpyAsync(h->rb_host, h->rebuilds, sizeof(int32_t), hipMemcpyDeviceToHost, h->st));
         HIPCHECK(hipEventRecord(h->rb_ev, h->st));
         h->rb_pending = true;

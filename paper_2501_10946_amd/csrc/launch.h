@@ -100,17 +100,21 @@ struct CellArgs {
     int32_t *tile_sum;     // [scan_tiles(ncell)], every kTilePad words: particles of each tile of cells, zero between builds
     int32_t *ticket;       // not read: the scan is one pass
     const int32_t *gate;   // null: always build; else build only when *gate != 0
-    int rare;              // the gate is closed in most launches (lists with a skin)
+    int rare;              // the gate has been seen to be open in few launches
 };
 __host__ __device__ inline int scan_tiles(int ncell) { return (ncell + kScanTile - 1) / kScanTile; }
 // Systems of at most kSmallBuildCells cells built by one workgroup in one launch:
 // up to kSmallBuildN particles always (rebuilt every step, us a step against the
 // three launches: N = 1000 30 and 37, 3000 36 and 39), up to kSmallBuildRareN
-// where the gate is mostly closed (N = 10 007, Gamma = 100: 23.5 and 31; Gamma = 10,
-// rebuilt every third step: 29 and 31; rebuilt at most steps, Gamma = 1: 35 and 32).
+// where at most one of N / kRareRows steps has been seen to rebuild.  A closed gate
+// saves 3 to 7 us a step (N = 10 007, Gamma = 100: 23.5 and 31), an open one costs
+// what one compute unit takes to move the rows (us a step rebuilt every step: N =
+// 4200 60 and 51, 8000 77 and 53, 16 384 122 and 56; every fifth: 32 and 33, 35 and
+// 33, 45 and 34; every tenth: 25 and 28, 25 and 28, 36 and 32).
 constexpr int kSmallBuildCells = 16384;
 constexpr int kSmallBuildN = 4096;
 constexpr int kSmallBuildRareN = 16384;
+constexpr int kRareRows = 1024;
 // ids + counts + snapshot, scan (which leaves the counts zero again), stable rank
 // + move (which leaves the tile sums zero); both must be zero on entry
 hipError_t launch_cell_build(const CellArgs &a, hipStream_t st);

@@ -105,6 +105,10 @@ struct rbsog_handle {
     hipEvent_t rb_ev;    // completes when rb_host holds the count of rb_steps steps
     bool rb_pending;
     int64_t rb_steps, steps_done;
+    // whether the gate was rarely open at the last look, and the steps and rebuilds it
+    // had seen by then
+    bool gate_rare = false;
+    int64_t look_steps = 0, look_rebuilds = 0;
     uint64_t samp_step;  // first step of the modes in samp, with samp_n steps drawn
     int samp_n;
     // Metropolis-Hastings draws (p.sampler == 1): the proposal CDF (F = 1) and
