@@ -1004,7 +1004,16 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
         }
         HIPCHECK(timed(h, kKickDrift, [&] { return launch_kick_drift(k, h->st); }));
     }
-    for (int n = 0; n < nsteps; ++n) {
+    int row0 = 0, filled = 0;   // the first row not added yet, the sets that wait for it
+    auto add_rows = [&] {
+        if (filled == 0) return (int)RBSOG_OK;
+        int rc = energy_rows(h, energy_hist_dev + kEnergyCols * (size_t)row0, filled, true, global);
+        if (rc) return rc;
+        row0 += filled;
+        filled = 0;
+        return (int)RBSOG_OK;
+    };
+    auto one_step = [&](int n) -> int {
         int32_t *gate = h->gate + h->phase, *gate_next = h->gate + (1 - h->phase);
         int rc = prepare(h, gate, true);
         if (rc) return rc;
@@ -1012,16 +1021,19 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
         uint64_t step = step0 + (uint64_t)n + 1;
         rc = modes(h, step, nsteps - n, &samp);
         if (rc) return rc;
-        const int eset = energy_hist_dev ? n % h->d.erows : -1;
+        const int eset = energy_hist_dev ? filled : -1;
         const bool last = n + 1 == nsteps;
         // a global bath keeps the next step's half-kick and drift out of the far
         // kernel: its velocity factor needs the whole system's kinetic energy
         rc = evaluate(h, samp, nullptr, nullptr, true, dt, eset, (last || global) ? nullptr : gate_next, gate, step + 1,
                       global ? (last ? 2 : 3) : 0);
         if (rc) return rc;
-        if (eset >= 0 && (last || eset + 1 == h->d.erows)) {   // the rows of the sets filled since the last time
-            rc = energy_rows(h, energy_hist_dev + kEnergyCols * (size_t)(n - eset), eset + 1, true, global);
-            if (rc) return rc;
+        if (eset >= 0) {
+            ++filled;
+            if (last || filled == h->d.erows) {
+                rc = add_rows();
+                if (rc) return rc;
+            }
         }
         if (global && !last) {
             KickDriftArgs k{};
@@ -1043,6 +1055,16 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
             HIPCHECK(timed(h, kKickDrift, [&] { return launch_kick_drift(k, h->st); }));
         }
         h->phase = 1 - h->phase;
+        return RBSOG_OK;
+    };
+    for (int n = 0; n < nsteps; ++n) {
+        const int rc = one_step(n);
+        if (rc == RBSOG_OK) continue;
+        std::string why;
+        why.swap(g_error);
+        (void)add_rows();   // the steps before the failure keep their rows
+        g_error.swap(why);
+        return rc;
     }
     if (global)   // the last step's closing half-step
         HIPCHECK(timed(h, kKickDrift, [&] { return launch_scale_v((int)h->p.N, h->vs, h->bath + 2, h->st); }));
