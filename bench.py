@@ -17,7 +17,8 @@ energy drift of each run (all steps, and the second half), per-kernel times from
 HIP events on the stream the kernels run on, the roofline position of the
 dominant kernel, the oracle's throughput on this machine's host cores, and the
 other workloads of the suite (N = 1000, N = 1e5 with pre-equilibration, the
-served ensemble, the binary mixture) as extra keys.
+served ensemble, the binary mixture) as extra keys.  The printed line summarises
+it; --detail FILE writes it all.
 """
 from __future__ import annotations
 
@@ -316,6 +317,44 @@ def strip(res: dict) -> dict:
     return {k: v for k, v in res.items() if k not in ("x", "v", "ehist", "system", "info", "step", "elapsed_s")}
 
 
+def headline(out: dict) -> dict:
+    """The line that is printed: the headline workload whole, a few figures of each other
+    measurement.  Short (under 2000 characters), so that what keeps only the end of a
+    run's output keeps all of it."""
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if d and k in d}
+
+    def rounded(v):
+        if isinstance(v, dict):
+            return {k: rounded(x) for k, x in v.items()}
+        if isinstance(v, (list, tuple)):
+            return [rounded(x) for x in v]
+        return float(f"{v:.5g}") if isinstance(v, float) else v
+
+    line = pick(out, "metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                "scaling", "vs_baseline", "dtype", "data")
+    def force(d):   # the whole force's errors, by coupling
+        return {g: e["total"] for g, e in d["force_rel_rms"].items() if e}
+
+    line["config"] = rounded(dict(out["config"], force_rel_rms=force(out["config"])))
+    short = {"mixed": dict(pick(out["mixed"], "value", "ms_per_step"), force_rel_rms=force(out["mixed"])),
+             "roofline": pick(out["roofline"], "kernel", "bound", "achieved", "peak", "unit", "frac", "traffic",
+                              "ms_per_launch") or None,
+             "cpu_baseline": pick(out["cpu_baseline"], "value", "unit", "cores", "kind") or None}
+    extra = {}
+    for name, r in out.get("extra", {}).items():
+        if name == "served":
+            extra[name] = pick(r["saturated"], "step_ms_p50", "step_ms_p99", "requests_per_s", "particle_steps_per_s")
+        elif "value" in r:
+            extra[name] = pick(r, "value", "ms_per_step")
+        elif "fp64" in r or "mixed" in r:
+            extra[name] = {k: r[k]["value"] for k in ("fp64", "mixed") if k in r}
+    if extra:
+        short["extra"] = extra
+    line.update(rounded(short))
+    return line
+
+
 def rooflines(kern: dict, work: dict) -> dict:
     """Every priced kernel: algorithmic slots per launch / mean launch time."""
     out = {}
@@ -546,6 +585,7 @@ def main():
     ap.add_argument("--serve-requests", type=int, default=256)
     ap.add_argument("--serve-rates", default="0.5,0.8,1.2",
                     help="Poisson arrival rates as fractions of the measured saturated capacity")
+    ap.add_argument("--detail", default="", help="file for everything measured (the line is a summary of it)")
     ap.add_argument("--serve-only", action="store_true",
                     help="only the served-ensemble measurement, printed as its own JSON line (for profiling)")
     ap.add_argument("--copy-calibration", type=float, default=0.0,
@@ -773,7 +813,10 @@ def main():
         if not args.no_serve:
             extra["served"] = serve(args, dev)
         out["extra"] = extra
-    print(json.dumps(out), flush=True)
+    if args.detail:
+        with open(args.detail, "w") as fh:
+            json.dump(out, fh, indent=1)
+    print(json.dumps(headline(out)), flush=True)
 
 
 if __name__ == "__main__":
