@@ -485,7 +485,9 @@ int rbsog_ens_bytes(const rbsog_params *p, const rbsog_sog *sog, int nsteps, siz
 
 /* Admits one replica: copies x, v (SoA [3][N]), q, m ([N]) from host memory
  * into the pool, computes its initial force and queues it for nsteps steps of
- * length dt.  *slot_out receives its slot.  Synchronises the stream.
+ * length dt.  *slot_out receives its slot.  The arrays are the caller's again on
+ * return; the uploads and the force evaluation are enqueued, ordered before the
+ * steps that follow, and the call does not wait for them.
  * Errors: RBSOG_EAGAIN (no free slot, or no contiguous pool range for its
  * workspace + state + energy history: retry after a retirement),
  * RBSOG_EINVAL, RBSOG_ENOROOT, RBSOG_EHIP. */
