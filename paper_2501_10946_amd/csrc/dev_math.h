@@ -73,24 +73,6 @@ constexpr Exp2Poly make_exp2_poly()
                      0x1.62bfc2c7ae40ep-20, 0x1.b524db38fd1f9p-24, 0x1.e6228bff026d1p-28, 0x1.ea044321bc0aap-32}};
 }
 
-// sin(2 pi f) = f sum_k s[k] f^(2k), s[k] = (-1)^k (2 pi)^(2k+1)/(2k+1)!, k = 0..8
-// cos(2 pi f) = sum_k c[k] f^(2k),    c[k] = (-1)^k (2 pi)^(2k)/(2k)!,     k = 0..8
-// For |f| <= 1/8 (|2 pi f| <= pi/4) the first omitted terms are below 2.1e-18.
-struct SinCosPoly {
-    double s[9];
-    double c[9];
-};
-constexpr SinCosPoly make_sincos_poly()
-{
-    SinCosPoly p{};
-    for (int k = 0; k < 9; ++k) {
-        double sg = (k % 2) ? -1.0 : 1.0;
-        p.s[k] = sg * taylor_coef(kTwoPi, 2 * k + 1);
-        p.c[k] = sg * taylor_coef(kTwoPi, 2 * k);
-    }
-    return p;
-}
-
 // 2^y for finite y <= 0 (FP64): 2^y = 2^n 2^f with n = rint(y), f = y - n exact.
 // Poly: Exp2Poly, in any address space.
 template <class Poly>
@@ -102,31 +84,6 @@ __device__ inline double exp2_nonpos(double y, const Poly &P)
 #pragma unroll
     for (int k = 10; k >= 0; --k) p = fma(p, f, P.c[k]);
     return ldexp(p, (int)n);
-}
-
-// sin(2 pi u), cos(2 pi u) for a phase u in revolutions (FP64).  The integer
-// and quarter-turn parts are removed exactly (u - rint(u) and r - q/4 are
-// exact in FP64), leaving f in [-1/8, 1/8]; the quarter turn q rotates the
-// result.
-__device__ inline void sincos_rev(double u, const SinCosPoly &P, double *s, double *c)
-{
-    double r = u - rint(u);
-    double q = rint(4.0 * r);
-    double f = fma(-0.25, q, r);
-    double f2 = f * f;
-    double sp = P.s[8], cp = P.c[8];
-#pragma unroll
-    for (int k = 7; k >= 0; --k) {
-        sp = fma(sp, f2, P.s[k]);
-        cp = fma(cp, f2, P.c[k]);
-    }
-    double sn = sp * f;
-    // rotate by q quarter turns, q in {-2, -1, 0, 1, 2}
-    int qi = (int)q & 3;
-    double s1 = (qi & 1) ? cp : sn;
-    double c1 = (qi & 1) ? sn : cp;
-    *s = (qi & 2) ? -s1 : s1;
-    *c = ((qi + 1) & 2) ? -c1 : c1;
 }
 
 constexpr int kPhaseTab = 128;   // entries of the rotation table

@@ -339,15 +339,6 @@ __device__ inline void near_add(NearSums &s, const PairTerms &t)
 // neighbour lists
 // ---------------------------------------------------------------------------
 
-// The value of v in lane l (l uniform), as a scalar.
-__device__ inline double readlane_f64(double v, int l)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // One wave lists the neighbours of the home particles of cell pair q,
 // kListHomes of them per pass over the window.  Lanes take 64 consecutive
 // candidates of the window at a time (loads coalesced along the rows); each
@@ -369,7 +360,6 @@ __device__ inline double readlane_f64(double v, int l)
 // scalar instructions a test, the launch took 0.54 ms).  N = 1e6 plasma: 0.44
 // -> 0.37 ms a build, 222 -> 169 M vector instructions.
 constexpr int kListHomes = 16;
-static_assert(kListBlock == 8, "a list block is read as two int4");
 
 // The tests of homes hp and hp + 1 of a pass against a chunk of 64 candidates
 // (one per lane: image-shifted position, its square, particle index j), and the
@@ -573,10 +563,8 @@ __device__ inline double dpp_add(double v)
 
 __device__ inline double share_sum(double v)
 {
-    v = dpp_add<0xB1>(v);                          // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E>(v);                          // quad_perm [2,3,0,1]
-    if (kNearShare >= 8) v = dpp_add<0x141>(v);    // row_half_mirror: the other quad of 8
-    if (kNearShare >= 16) v = dpp_add<0x140>(v);   // row_mirror: the other half of 16
+    v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
     return v;
 }
 
@@ -589,7 +577,7 @@ template <bool MIXED, bool ENERGY, int NG, bool SPLIT = true>
 __device__ inline void near_body(NearMem &a0, int lb)
 {
     NearMem &a = near_args_again(a0);
-    static_assert(kNearShare == 4 || kNearShare == 8 || kNearShare == 16, "share_sum adds 4, 8 or 16 lanes");
+    static_assert(kNearShare == 4, "share_sum adds 4 lanes");
     const int t = threadIdx.x, sub = t & (kNearShare - 1);
     const int rows = list_rows(a.kp);
     const int p = lb * kNearHomes + t / kNearShare;

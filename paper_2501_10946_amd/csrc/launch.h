@@ -98,7 +98,7 @@ struct CellArgs {
     int32_t *fill;         // [ncell] the run of rows that the id pass put last into each cell
     int32_t *tmp;          // [N] by a run's first row: the run of its cell before it
     int32_t *tile_sum;     // [scan_tiles(ncell)], every kTilePad words: particles of each tile of cells, zero between builds
-    int32_t *ticket;       // not read: the scan is one pass
+    int32_t *ticket;       // not read by the kernels, but a build without it is refused
     const int32_t *gate;   // null: always build; else build only when *gate != 0
     int rare;              // the gate has been seen to be open in few launches
 };
@@ -370,7 +370,7 @@ struct FarArgs {
     double *kepart;            // [far_blocks(N)] kinetic-energy partials (when vs)
     int *flag;                 // set to 1 on a non-finite force
     int mixed;
-    const double2 *tab;        // not read: the FP64 phases take a polynomial (ss)
+    const double2 *tab;        // not read by the kernels: the FP64 phases take a polynomial (ss)
     SinPoly ss;
     int32_t *gate_clear;       // null, or a rebuild gate to clear (nothing later in the step reads it)
     int32_t *rebuilds;         // null, or a count of the steps whose gate was raised (with gate_clear)

@@ -94,7 +94,7 @@ struct rbsog_handle {
     int32_t *nbr, *nbr_cnt;
     int32_t *gate;       // device, two words: rebuild the cell order and lists in this step
                          // (steps alternate between them; each step clears the other)
-    int32_t *ticket;     // device: the scan's finished-tile counter
+    int32_t *ticket;     // device: a spare word (CellArgs::ticket)
     int phase;           // which gate word the next step uses
     bool lists_valid;    // cell order and lists in the workspace belong to the fine grid
     double m_min;        // lightest mass (host copy, for the default skin's thermal check)
