@@ -226,6 +226,10 @@ __device__ inline double2 rho_group(const RhoArgs &a, const double2 *tab, const 
     return UNIT ? make_double2(re0 + re1 - rs, im0 + im1 + is) : make_double2(re0 + re1, im0 + im1);
 }
 
+// groups of fewer particles are summed with their charges: asking whether these are
+// all equal takes longer than it saves
+constexpr int kUnitChunk = 64;
+
 template <bool CELL, bool MIXED, bool FINE>
 __device__ inline void rho_partial_body(const RhoArgs &a, int b)
 {
@@ -242,14 +246,15 @@ __device__ inline void rho_partial_body(const RhoArgs &a, int b)
     const int j_hi = min(a.N, (s_hi + 1) * a.chunk);
     // every particle of the workgroup with one charge (a one-component plasma):
     // the sums run without it
-    const double q0 = CELL ? a.xs[j_lo].w : a.q[j_lo];
+    const bool ask = !MIXED && a.chunk >= kUnitChunk;   // uniform over the launch
+    const double q0 = !ask ? 0.0 : CELL ? a.xs[j_lo].w : a.q[j_lo];
     bool other = false;
     for (int k = t; k < j_hi - j_lo; k += kBlock) {
         int j = j_lo + k;
         double4 v;
         if (CELL) v = a.xs[j];
         else v = make_double4(a.x[j], a.x[a.N + j], a.x[2 * a.N + j], a.q[j]);
-        other |= !(v.w == q0);
+        if (!MIXED) other |= !(v.w == q0);
         double x = v.x * a.inv_L[0], y = v.y * a.inv_L[1], z = v.z * a.inv_L[2];
         if (!MIXED) {
             x = less_turns(v.x, a.inv_L[0]);
@@ -262,7 +267,9 @@ __device__ inline void rho_partial_body(const RhoArgs &a, int b)
         const double2 *src = FINE ? a.tab_fine : a.tab;
         for (int k = t; k < T; k += kBlock) tab[k] = src[k];
     }
-    const bool unit = !__syncthreads_or(other) && !MIXED;   // uniform
+    bool unit = false;   // uniform
+    if (ask) unit = !__syncthreads_or(other);
+    else __syncthreads();
     const int64_t g = g0 + t;
     if (g >= (int64_t)a.nchunk * a.P) return;
     const int s = (int)(g / a.P), l = (int)(g - (int64_t)s * a.P);
