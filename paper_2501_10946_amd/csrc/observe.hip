@@ -102,6 +102,7 @@ struct RdfArgs {
     double w[3];              // its cell widths
     const double4 *xs;        // cell order
     const int32_t *cell_start;
+    int own;                  // passes of a cell pair that its own wave takes
     double rmax2, dr;
     unsigned long long *hist;
 };
@@ -142,18 +143,80 @@ __device__ inline RdfChunk rdf_chunk(const RdfArgs &a, const PairTables &w, cons
     return o;
 }
 
-// Each wave takes cell pairs of the fine grid in turn, as the list build does: the
-// candidates of a pair's 5 x 5 x 6-cell window 64 at a time (image-shifted, each
-// neighbour within r_max <= L/3 met once) against the pair's home particles.  The
-// squared distances below r_max^2 (a fifth or so) are queued in LDS and binned 64
-// at a time, so that the square root and the division run on full waves; a
-// workgroup's counts go through LDS, then one atomic add per non-empty bin.
-// Integer counts: the result does not depend on the order of the additions.
+// One wave's work on cell pair q, as the list build does it: the candidates of the pair's
+// 5 x 5 x 6-cell window 64 at a time (image-shifted, each neighbour within r_max <= L/3
+// met once) against the pair's home particles, kRdfHomes per pass over the window: the
+// passes first, first + step, ... before end.  The squared distances below r_max^2 (a
+// fifth or so) are queued in LDS and binned 64 at a time, so that the square root and the
+// division run on full waves.
+__device__ inline void rdf_pair(const RdfArgs &a, int q, int first, int step, int end, PairTables &w, double4 *home,
+                                double *qu, uint8_t *pidx, unsigned long long *h, int &queued)
+{
+    const int lane = threadIdx.x & 63;
+    PairWindow win;
+    double centre[3];
+    if (!pair_window<false>(a.g, a.w, a.cell_start, q, w, centre, win)) return;   // uniform
+    const int total = win.total;
+    const bool tabled = window_pieces(w, total, pidx);
+    const int home_c = win.h_beg - __builtin_amdgcn_readfirstlane(w.first[pair_window_home_piece(a.g, q)]);
+    const int passes = min(end, (win.h_end - win.h_beg + kRdfHomes - 1) / kRdfHomes);
+    for (int p = first; p < passes; p += step) {
+        const int hb = win.h_beg + p * kRdfHomes;
+        const int nh = min(kRdfHomes, win.h_end - hb);   // uniform
+        if (lane < nh) home[lane] = a.xs[hb + lane];
+        wave_lds_fence();
+        const int hc = home_c + (hb - win.h_beg);   // candidate index of the pass's first home
+        // the next 64 candidates load while these are tested
+        RdfChunk next = rdf_chunk(a, w, pidx, tabled, 0, total);
+        for (int c0 = 0; c0 < total; c0 += 64) {
+            const RdfChunk cur = next;
+            if (c0 + 64 < total) next = rdf_chunk(a, w, pidx, tabled, c0 + 64, total);
+            const uint64_t live = __builtin_amdgcn_ballot_w64(c0 + lane < total);
+            const int own = c0 + lane - hc;   // the pass's home this lane holds (any other value: none)
+            for (int hp = 0; hp < nh; hp += 2) {   // two at a time: their LDS reads overlap
+                const double4 r[2] = {home[hp], home[min(hp + 1, nh - 1)]};
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if (hp + i >= nh) break;   // uniform
+                    const double ux = r[i].x - cur.x, uy = r[i].y - cur.y, uz = r[i].z - cur.z;
+                    const double r2 = fma(uz, uz, fma(ux, ux, uy * uy));
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(r2 < a.rmax2) & live &
+                                       __builtin_amdgcn_ballot_w64(own != hp + i);
+                    const uint32_t k = __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)queued));
+                    if (__builtin_amdgcn_inverse_ballot_w64(m)) qu[k] = r2;   // queued < 64: k < 128
+                    queued += __popcll(m);
+                    if (queued >= 64) {   // uniform
+                        wave_lds_fence();
+                        rdf_count(a, qu, 64, h);
+                        queued -= 64;
+                        const double rest = qu[64 + lane];
+                        wave_lds_fence();
+                        qu[lane] = rest;   // those past `queued` are written over
+                        wave_lds_fence();
+                    }
+                }
+            }
+        }
+        wave_lds_fence();   // the next pass overwrites the homes
+    }
+}
+
+// The cell pairs of the fine grid are dealt to the waves in turn, each with its first
+// passes (a.own: what nearly every pair of a uniform system needs).  The passes that are
+// left in crowded pairs are dealt to kRdfSlices waves: each looks through a share of the
+// pairs, spread over the grid, a lane per pair, and takes its turn.  A workgroup's counts go through LDS,
+// then one atomic add per non-empty bin.  Integer counts: the result does not depend on
+// the order of the additions.
 //
 // One particle per thread walking its own 125 cells left most lanes idle at the
 // ends of cells of ~3 particles and divided on the lanes that passed: N = 2e5, r_max
 // = 4, 200 bins took 307 us, this takes 131 (vector instructions issue in half of
-// its cycles; the latency of the window tables takes most of the rest).
+// its cycles; the latency of the window tables takes most of the rest).  Dealt by whole
+// pairs, neighbouring pairs to a workgroup, a cluster was left to a few waves: 6000 of
+// 20 000 particles in a sphere of 1.5 took 108 ms, 2e5 in one of 20 14 ms.
+constexpr int kRdfSlices = 64;
+
 __global__ __launch_bounds__(kRdfThreads) void k_rdf(RdfArgs a)
 {
     extern __shared__ unsigned long long h[];   // [nbins]
@@ -165,60 +228,37 @@ __global__ __launch_bounds__(kRdfThreads) void k_rdf(RdfArgs a)
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    PairTables &w = tabs[wv];
-    double *qu = queue[wv];
     int queued = 0;   // uniform
-    const int64_t pairs = (int64_t)a.g.nc[2] * a.g.nc[1] * ((a.g.nc[0] + 1) >> 1);
-    const int q0 = (int)(pairs * blockIdx.x / gridDim.x), q1 = (int)(pairs * (blockIdx.x + 1) / gridDim.x);
-    for (int q = q0 + wv; q < q1; q += kRdfWaves) {
-        PairWindow win;
-        double centre[3];
-        if (!pair_window<false>(a.g, a.w, a.cell_start, q, w, centre, win)) continue;   // uniform
-        const int total = win.total;
-        const bool tabled = window_pieces(w, total, pidx[wv]);
-        const int home_c = win.h_beg - __builtin_amdgcn_readfirstlane(w.first[pair_window_home_piece(a.g, q)]);
-        for (int hb = win.h_beg; hb < win.h_end; hb += kRdfHomes) {
-            const int nh = min(kRdfHomes, win.h_end - hb);   // uniform
-            if (lane < nh) home[wv][lane] = a.xs[hb + lane];
-            wave_lds_fence();
-            const int hc = home_c + (hb - win.h_beg);   // candidate index of the pass's first home
-            // the next 64 candidates load while these are tested
-            RdfChunk next = rdf_chunk(a, w, pidx[wv], tabled, 0, total);
-            for (int c0 = 0; c0 < total; c0 += 64) {
-                const RdfChunk cur = next;
-                if (c0 + 64 < total) next = rdf_chunk(a, w, pidx[wv], tabled, c0 + 64, total);
-                const uint64_t live = __builtin_amdgcn_ballot_w64(c0 + lane < total);
-                const int own = c0 + lane - hc;   // the pass's home this lane holds (any other value: none)
-                for (int hp = 0; hp < nh; hp += 2) {   // two at a time: their LDS reads overlap
-                    const double4 r[2] = {home[wv][hp], home[wv][min(hp + 1, nh - 1)]};
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        if (hp + i >= nh) break;   // uniform
-                        const double ux = r[i].x - cur.x, uy = r[i].y - cur.y, uz = r[i].z - cur.z;
-                        const double r2 = fma(uz, uz, fma(ux, ux, uy * uy));
-                        const uint64_t m = __builtin_amdgcn_ballot_w64(r2 < a.rmax2) & live &
-                                           __builtin_amdgcn_ballot_w64(own != hp + i);
-                        const uint32_t k = __builtin_amdgcn_mbcnt_hi(
-                            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)queued));
-                        if (__builtin_amdgcn_inverse_ballot_w64(m)) qu[k] = r2;   // queued < 64: k < 128
-                        queued += __popcll(m);
-                        if (queued >= 64) {   // uniform
-                            wave_lds_fence();
-                            rdf_count(a, qu, 64, h);
-                            queued -= 64;
-                            const double rest = qu[64 + lane];
-                            wave_lds_fence();
-                            qu[lane] = rest;   // those past `queued` are written over
-                            wave_lds_fence();
-                        }
-                    }
-                }
-            }
-            wave_lds_fence();   // the next pass overwrites the homes
+    auto pair = [&](int q, int first, int step, int end) {
+        rdf_pair(a, q, first, step, end, tabs[wv], home[wv], queue[wv], pidx[wv], h, queued);
+    };
+    const int half = (a.g.nc[0] + 1) >> 1, pairs = a.g.nc[2] * a.g.nc[1] * half;
+    const int blocks = (int)gridDim.x, waves = blocks * kRdfWaves;
+    // neighbouring pairs to a workgroup (they share most of their rows) where a wave has one
+    // at most (N = 2e4: 49 us a histogram with its build, 51 apart), else far apart
+    const bool apart = pairs > waves;
+    for (int q = (int)blockIdx.x * (apart ? 1 : kRdfWaves) + wv * (apart ? blocks : 1); q < pairs; q += waves)
+        pair(q, 0, 1, a.own);
+    const int slices = min(kRdfSlices, waves), shares = waves / slices, columns = (pairs + 63) / 64;
+    const int wave = (int)blockIdx.x * kRdfWaves + wv;
+    int turn = wave % slices;   // this wave's place in the deal of its share's passes, less what is dealt (mod slices)
+    for (int col = wave / slices; col < columns && wave < shares * slices; col += shares) {
+        const int q = lane * columns + col;
+        int left = 0;
+        if (q < pairs) {
+            const int row = q / half, x0 = 2 * (q - row * half), x1 = min(x0 + 1, a.g.nc[0] - 1);
+            const int32_t *start = a.cell_start + row * a.g.nc[0];
+            left = max(0, (start[x1 + 1] - start[x0] + kRdfHomes - 1) / kRdfHomes - a.own);
+        }
+        for (uint64_t m = __builtin_amdgcn_ballot_w64(left > 0); m != 0; m &= m - 1) {   // uniform
+            const int l = (int)__builtin_ctzll(m);
+            pair(l * columns + col, a.own + turn, slices, 0x7fffffff);
+            turn -= __builtin_amdgcn_readlane(left, l) % slices;
+            if (turn < 0) turn += slices;
         }
     }
     wave_lds_fence();
-    rdf_count(a, qu, queued, h);
+    rdf_count(a, queue[wv], queued, h);
     __syncthreads();
     for (int b = threadIdx.x; b < a.nbins; b += kRdfThreads)
         if (h[b]) atomicAdd(&a.hist[b], h[b]);
@@ -438,6 +478,9 @@ extern "C" int rbsog_rdf(rbsog_handle *h, const double *x_dev, double r_max, int
     for (int d = 0; d < 3; ++d)
         if (a.g.nc[d] < 6) return fail(RBSOG_EINVAL, "fine grid of %d cells is below the 6-cell window", a.g.nc[d]);
     const int pairs = a.g.nc[2] * a.g.nc[1] * ((a.g.nc[0] + 1) / 2);
+    // home particles of a pair at uniform density, and four deviations of their number
+    const double mean = 2.0 * (double)h->p.N / (double)a.g.ncell;
+    a.own = (int)std::ceil((mean + 4.0 * std::sqrt(mean)) / kRdfHomes);
     hipLaunchKernelGGL(k_rdf, dim3(std::min(kRdfBlocks, (pairs + kRdfWaves - 1) / kRdfWaves)), dim3(kRdfThreads),
                        sizeof(unsigned long long) * (size_t)nbins, h->st, a);
     HIPCHECK(hipGetLastError());
