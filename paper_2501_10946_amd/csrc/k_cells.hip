@@ -238,13 +238,27 @@ RBSOG_KERNELS(rank, CellArgs, kBlock)
 constexpr int kSmallThreads = 1024;
 static_assert(kSmallBuildN == 4 * kSmallThreads && kSmallBuildRareN == 16 * kSmallThreads, "rows per thread");
 
+// How many of v[from .. to) are less than key, four to a read where v is aligned: a
+// thread reads all of its cell, and all of a clump's threads read all of the clump.
+__device__ inline int below(const int32_t *v, int from, int to, int key)
+{
+    int r = 0, m = from;
+    for (; m < to && (m & 3); ++m) r += v[m] < key;
+    for (; m + 3 < to; m += 4) {
+        const int4 u = *(const int4 *)(v + m);
+        r += (u.x < key) + (u.y < key) + (u.z < key) + (u.w < key);
+    }
+    for (; m < to; ++m) r += v[m] < key;
+    return r;
+}
+
 template <int ROWS, bool HOLD>
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(CellArgs a)
 {
     if (!gate_open(a.gate)) return;
     constexpr int kMax = ROWS * kSmallThreads;
     __shared__ int32_t start[kSmallBuildCells];   // counts, then the cells' first positions
-    __shared__ int32_t member[kMax];              // caller indices by cell, unordered
+    __shared__ __align__(16) int32_t member[kMax];   // caller indices by cell, unordered
     __shared__ int32_t wsum[kSmallThreads / 64];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     for (int c = t; c < a.g.ncell; c += kSmallThreads) start[c] = 0;
@@ -307,8 +321,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(CellArgs a)
         if (p < a.N) {
             const int cb = start[id[k]], ce = id[k] + 1 < a.g.ncell ? start[id[k] + 1] : a.N;
             const int key = HOLD ? row[HOLD ? k : 0].order : a.order_old[p];
-            int r = 0;
-            for (int m = cb; m < ce; ++m) r += (member[m] < key);
+            const int r = below(member, cb, ce, key);
             if constexpr (HOLD) place_row(a, row[k], cb + r);
             else place_row(a, old_row(a, p), cb + r);
         }
