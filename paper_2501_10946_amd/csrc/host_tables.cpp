@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <utility>
 
 #include "internal.h"
 
@@ -298,20 +299,21 @@ void build_tables(const rbsog_sog &s, const rbsog_params &p, double Q2, int mmax
     for (int i = 0; i < t->nshell; ++i) t->coef.push_back(t->S / ((double)p.P * V * Fk_of[i]));
 }
 
-// (sin, cos)(2 pi j / n), j < n, to the nearest FP64 value: from 2 pi j / n in the 64
-// bits of long double (an FP64 angle is up to an ulp of 2 pi off, and the entries with
-// it by 2e-16, the size of the other errors of a structure-factor term)
+// (sin, cos)(2 pi j / n), j < n (a multiple of 8), to the nearest FP64 value: the first
+// eighth from 2 pi j / n in the 64 bits of long double (an FP64 angle is up to an ulp of
+// 2 pi off, and the entries with it by 2e-16, the size of the other errors of a
+// structure-factor term), the rest by symmetry
 static void rotation_table(double *out, int n)
 {
     const long double two_pi = 6.283185307179586476925286766559L;
     for (int j = 0; j < n; ++j) {
-        const long double a = two_pi * j / n;
-        double s = (double)sinl(a), c = (double)cosl(a);
-        if (j == n / 4) { s = 1.0; c = 0.0; }
-        if (j == n / 2) { s = 0.0; c = -1.0; }
-        if (j == 3 * n / 4) { s = -1.0; c = 0.0; }
-        out[2 * j] = s;
-        out[2 * j + 1] = c;
+        const int turn = j / (n / 4), r = j % (n / 4), m = r > n / 8 ? n / 4 - r : r;
+        const bool first = turn == 0 && r <= n / 8;
+        double s = first ? (double)sinl(two_pi * m / n) : out[2 * m];
+        double c = first ? (double)cosl(two_pi * m / n) : out[2 * m + 1];
+        if (r > n / 8) std::swap(s, c);
+        out[2 * j] = (turn == 0 ? s : turn == 1 ? c : turn == 2 ? -s : -c) + 0.0;   // no -0
+        out[2 * j + 1] = (turn == 0 ? c : turn == 1 ? -s : turn == 2 ? -c : s) + 0.0;
     }
 }
 
