@@ -107,9 +107,8 @@ constexpr SinCosShort make_sincos_short()
     return p;
 }
 
-
 // sin(2 pi w / 128), cos(2 pi w / 128) for a phase w in 1/128 revolutions
-// (FP64; the callers scale positions by 128 / L, exactly) with a table of
+// (FP64; the callers scale modes or positions by 128, exactly) with a table of
 // (sin, cos)(2 pi j / 128): w = m + f exactly with m = rint(w) and |f| <= 1/2
 // (for |w| < 2^52 the difference is exact), the short series give the rotation
 // by f and the table entry of m mod 128 (in LDS) the rest.
