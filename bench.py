@@ -67,9 +67,9 @@ def slots_far(pr: dict) -> float:
 # Sources each profiled kernel is built from: a stored counter figure holds
 # only while the SHA-256 over these files is the one it was taken on.
 KERNEL_SOURCES = {
-    "near": ["k_near.hip", "k_rho.hip", "dev_common.h", "dev_math.h", "launch.h"],
+    "near": ["k_near.hip", "k_rho.hip", "dev_common.h", "dev_math.h", "dev_window.h", "launch.h"],
     "far": ["k_far.hip", "dev_common.h", "dev_math.h", "launch.h"],
-    "nlist": ["k_near.hip", "dev_common.h", "launch.h"],
+    "nlist": ["k_near.hip", "dev_common.h", "dev_math.h", "dev_window.h", "launch.h"],
 }
 
 # HBM bytes per launch at the N = 1e6, Gamma = 0.1 plasma (FP64), from one
@@ -79,9 +79,9 @@ KERNEL_SOURCES = {
 # WRITE_SIZE 262147 KiB for 262144 KiB written: x1.000).
 MEASURED_TRAFFIC = {
     # kernel: (sources sha256, FETCH_SIZE KiB, WRITE_SIZE KiB, fetch scale, write scale)
-    "near": ("bc4d6e53a0cfa472b8adb77c2f111b2f82bc2225ffd6e094f8653ae4802d0387", 417528.0, 53961.0, 2.0, 1.0),
-    "far": ("bf2f60c322b81bd10ede99699c6392fb364ae7ea6ef296dc67de0602e1996c82", 55492.0, 78392.0, 2.0, 1.0),
-    "nlist": ("65c2fe290e18411a1516ad105766501f64b9441aa9cfa2b1d5b7f05d28c0dcf7", 83838.0, 517244.0, 2.0, 1.0),
+    "near": ("c41f0490f71d5a0f7d71b49be41611d222c471a2a1971bb9d8826143b7738200", 417569.0, 53961.0, 2.0, 1.0),
+    "far": ("fcf864462b2e99e73dea24821999ca078272f41f35907c4cbba07f7ee734789c", 55426.0, 78392.0, 2.0, 1.0),
+    "nlist": ("ee3821b3f494244cf7a60255b4164abe7b5c7c4d4bc366ed62e4213bd2940784", 83839.0, 517199.0, 2.0, 1.0),
 }
 
 # VALU issue at the same workload (FP64): VALU busy = SQ_ACTIVE_INST_VALU x 4
@@ -90,9 +90,9 @@ MEASURED_TRAFFIC = {
 # fraction of the VALU's lane-cycles that issued work.
 MEASURED_VALU = {
     # kernel: (sources sha256, VALU busy, lane utilisation)
-    "near": ("bc4d6e53a0cfa472b8adb77c2f111b2f82bc2225ffd6e094f8653ae4802d0387", 0.79, 0.97),
-    "far": ("bf2f60c322b81bd10ede99699c6392fb364ae7ea6ef296dc67de0602e1996c82", 0.91, 1.00),
-    "nlist": ("65c2fe290e18411a1516ad105766501f64b9441aa9cfa2b1d5b7f05d28c0dcf7", 0.76, 0.75),
+    "near": ("c41f0490f71d5a0f7d71b49be41611d222c471a2a1971bb9d8826143b7738200", 0.79, 0.97),
+    "far": ("fcf864462b2e99e73dea24821999ca078272f41f35907c4cbba07f7ee734789c", 0.91, 1.00),
+    "nlist": ("ee3821b3f494244cf7a60255b4164abe7b5c7c4d4bc366ed62e4213bd2940784", 0.76, 0.75),
 }
 
 

@@ -211,7 +211,7 @@ __device__ inline void rdf_pair(const RdfArgs &a, int q, int first, int step, in
 //
 // One particle per thread walking its own 125 cells left most lanes idle at the
 // ends of cells of ~3 particles and divided on the lanes that passed: N = 2e5, r_max
-// = 4, 200 bins took 307 us, this takes 131 (vector instructions issue in half of
+// = 4, 200 bins took 307 us, this takes 121 (vector instructions issue in half of
 // its cycles; the latency of the window tables takes most of the rest).  Dealt by whole
 // pairs, neighbouring pairs to a workgroup, a cluster was left to a few waves: 6000 of
 // 20 000 particles in a sphere of 1.5 took 108 ms, 2e5 in one of 20 14 ms.
