@@ -1073,7 +1073,9 @@ extern "C" int rbsog_step(rbsog_handle *h, double *x_dev, double *v_dev, double 
     if (h->rb_host && h->skin_default && h->d.skin > 0.0) {
         // the count of the call before, if it came too late for this one's start: calls
         // that follow one another at once would never see one
-        if (h->rb_pending && hipEventQuery(h->rb_ev) == hipSuccess) look_at_gate(h);
+        if (h->rb_pending && h->p.N > kSmallBuildN && h->p.N <= kSmallBuildRareN &&
+            hipEventQuery(h->rb_ev) == hipSuccess)
+            look_at_gate(h);
         HIPCHECK(hipMemcpyAsync(h->rb_host, h->rebuilds, sizeof(int32_t), hipMemcpyDeviceToHost, h->st));
         HIPCHECK(hipEventRecord(h->rb_ev, h->st));
         h->rb_pending = true;
